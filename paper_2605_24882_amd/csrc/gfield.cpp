@@ -321,11 +321,11 @@ struct Workspace {
   DBuf<int> active0;
   DBuf<ColState> cs;
   DBuf<double> partial;
-  DBuf<int> counter;
+  int ncols = 0;  // columns of the current batch (the rest of ldb pads the last tile)
   std::vector<int> active_h;
   uint64_t last = 0;   // the space's call that used it last
   size_t bytes = 0;    // device memory it holds
-  Scratch scratch() { return Scratch{partial.p, counter.p}; }
+  Scratch scratch() { return Scratch{partial.p, ncols}; }
 };
 
 }  // namespace gf
@@ -413,7 +413,6 @@ static Workspace &get_workspace(gf_space *sp, int ldb, int prec, int slot = 0) {
   w->active0.alloc(w->ntiles);
   w->cs.alloc(ldb);
   w->partial.alloc(scratch_slots(sp, ldb, w->ntiles) * ldb);
-  w->counter.alloc(w->ntiles);
   std::vector<double> ones(ldb, 1.0);
   std::vector<float> onesf(ldb, 1.0f);
   w->one64.upload(ones, sp->ctx->stream);
@@ -586,7 +585,7 @@ static const ApplyTune &get_tune_p32(const Level &L, int ldb, int ntiles, const 
     e.y = ty_.p;
     e.dot = 1;
     e.op = OP_ALPHA;  // into the scratch states
-    Scratch sc{part.p, nullptr};
+    Scratch sc{part.p};
     hipEvent_t e0, e1;
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
@@ -738,11 +737,9 @@ static Plan &get_plan(gf_space *sp, const std::vector<double> &sig) {
   dsig.upload(hsig, s);
   one.upload(ones, s);
   DBuf<double> partial;
-  DBuf<int> counter;
   partial.alloc((size_t)2 * kMaxRowBlocks * ldb);
-  counter.alloc(nt);
   out.alloc((size_t)2 * ldb);
-  Scratch sc{partial.p, counter.p};
+  Scratch sc{partial.p};
   pl->invb.assign(sp->nlev(), std::vector<double>(nn, 0.0));
   pl->mshare.assign(sp->nlev(), std::vector<double>(nn, 0.0));
   pl->ia_mass = 1.0 / mass_interval_ratio(sp->p);
@@ -1047,6 +1044,7 @@ struct BatchSolve {
   void prepare(hipStream_t s) {
     const Level &F = sp->fine();
     const int ldb = w->ldb;
+    w->ncols = spec.ncols;
     if (spec.cheb_auto)
       spec.cheb = concurrent > 1 ? kDefaultChebConcurrent
                   : ((double)spec.ncols * F.N < kSmallBatchWork || spec.rough_load) ? kDefaultChebSmall
@@ -1341,7 +1339,7 @@ static std::string graph_key(const std::vector<BatchSolve *> &items, int chunk) 
     const SolveSpec &sp = it->spec;
     os << "|" << (const void *)it->sp << "," << (const void *)sp.plan << "," << (const void *)&w << "," << w.ldb
        << "," << sp.prec << "," << sp.kind << "," << sp.cheb << "," << sp.rtol << "," << sp.max_iter << ","
-       << sp.flags << "," << sp.precond << "," << sp.mass_shift << "," << sp.smooth_load << "," << w.nslot << ","
+       << sp.flags << "," << w.ncols << "," << sp.precond << "," << sp.mass_shift << "," << sp.smooth_load << "," << w.nslot << ","
        << w.rows16 << "," << it->p32 << "," << (const void *)w.x.p << "," << (const void *)w.r.p << ","
        << (const void *)w.p.p << "," << (const void *)w.p32.p << "," << (const void *)w.q.p << "," << (const void *)w.cs.p << "," << (const void *)w.partial.p << ","
        << (const void *)w.active.p << "," << (const void *)w.sig64.p;

@@ -22,15 +22,14 @@ enum ReduceOp { OP_STORE = 0, OP_BB, OP_RZ0, OP_ALPHA, OP_CHECK, OP_BETA, OP_BET
 constexpr int kMaxRowBlocks = 1024;  // row blocks of the generic reduction kernels
 constexpr int kRowBlocks = 256;      // row blocks per column tile of the streaming kernels
 
-// partial sums [slots][ldb] and one counter per column tile
+// partial sums [slots][ldb]; the batch's own columns (0: all; the others pad the last tile)
 struct Scratch {
   double *partial = nullptr;
-  int *counter = nullptr;
+  int ncols = 0;
 };
 
-// Per-system scalar step applied by the last block of a column tile to the reduced sums.
-__device__ inline void finalize_col(int op, int col, const double *tot, ColState *cs, double tol2, int maxit) {
-  ColState &c = cs[col];
+// Per-system scalar step on the reduced sums of a column.
+__device__ inline void finalize_col(int op, ColState &c, const double *tot, double tol2, int maxit) {
   switch (op) {
     case OP_BB:
       c.bb = tot[0];
@@ -85,32 +84,12 @@ __device__ inline void finalize_col(int op, int col, const double *tot, ColState
       c.rz = tot[0];
       break;
     case OP_CHECK_BETA:  // tot[0] = |r|^2 (the test), tot[1] = r.z (beta), as OP_CHECK then OP_BETA
-      finalize_col(OP_CHECK, col, tot, cs, tol2, maxit);
-      finalize_col(OP_BETA, col, tot + 1, cs, tol2, maxit);
+      finalize_col(OP_CHECK, c, tot, tol2, maxit);
+      finalize_col(OP_BETA, c, tot + 1, tol2, maxit);
       break;
     default:
       break;
   }
-}
-
-// Sum of the per-block partials of one column tile, by all 256 threads of the last block: wavefront w
-// adds slots w, w+4, w+8, ... (four independent chains), then the four wavefront sums are added in
-// order.  The partition depends only on nslot, so the result is bitwise reproducible.
-__device__ inline double sum_partials(const double *partial, int nslot, int ldb, int col) {
-  __shared__ double red_sp[4][64];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-  int b = w;
-  for (; b + 12 < nslot; b += 16) {
-    s0 += partial[(int64_t)b * ldb + col];
-    s1 += partial[(int64_t)(b + 4) * ldb + col];
-    s2 += partial[(int64_t)(b + 8) * ldb + col];
-    s3 += partial[(int64_t)(b + 12) * ldb + col];
-  }
-  for (; b < nslot; b += 4) s0 += partial[(int64_t)b * ldb + col];
-  red_sp[w][lane] = (s0 + s1) + (s2 + s3);
-  __syncthreads();
-  return ((red_sp[0][lane] + red_sp[1][lane]) + red_sp[2][lane]) + red_sp[3][lane];
 }
 
 // per-system scalar step over the partials of a reduction (k_fused.hip)
