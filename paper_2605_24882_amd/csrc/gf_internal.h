@@ -143,6 +143,10 @@ struct Level {
   DBuf<uint8_t> owner;              // [R] 1 on the owner copy of each unknown
   DBuf<int> grp_ptr, grp_rows;      // shared unknowns: CSR list of their rows
   int ngroups = 0;
+  // patch coefficients (m, iy, ix) in order: padded row, and position in grp_rows (-1: not shared); and
+  // the rows of grp_rows as patch coefficients
+  DBuf<int> crow, cpos, grp_coef;
+  int ncopies = 0;
   DBuf<int> owner_row;              // [N] row of the owner copy
   DBuf<int> row_gid;                // [R] global id of a row (-1 on ghosts)
   // prolongation from the next coarser level into this level (empty on level 0 of the space)

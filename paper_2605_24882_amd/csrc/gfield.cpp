@@ -139,6 +139,18 @@ static void build_level_device(gf_space *sp, Level &L, const SurfaceArgs &surf) 
     L.grp_ptr.upload(gp, s);
     L.grp_rows.upload(gr, s);
   }
+  std::vector<int> crow, cpos((size_t)L.npatch * n1 * n1, -1), gc;
+  for (int64_t r = 0; r < L.R; ++r)
+    if (row_gid[r] >= 0) crow.push_back((int)r);
+  for (int r : gr) {
+    const int m = r / (W * W), q = r % (W * W);
+    gc.push_back((m * n1 + q / W - p) * n1 + q % W - p);
+    cpos[gc.back()] = (int)gc.size() - 1;
+  }
+  L.ncopies = (int)gc.size();
+  L.crow.upload(crow, s);
+  L.cpos.upload(cpos, s);
+  L.grp_coef.upload(gc, s);
 
   // patch stencils by probing the matrix-free operator: 2 S^2 probe columns (M then S)
   const int ldb = round_up(2 * L.S * L.S, CT);
@@ -440,6 +452,8 @@ struct Prec<double> {
   static double *zb(LevelWork &l) { return l.z64b.p; }
   static double *a(LevelWork &l) { return l.a64.p; }
   static const double *cf(LevelWork &l) { return l.cf64.p; }
+  static const double *res(const Level &L) { return L.res_c.p; }
+  static const double *pro(const Level &L) { return L.pro_c.p; }
   static double *sig(Workspace &w) { return w.sig64.p; }
   static double *one(Workspace &w) { return w.one64.p; }
 };
@@ -454,6 +468,8 @@ struct Prec<float> {
   static float *zb(LevelWork &l) { return l.z32b.p; }
   static float *a(LevelWork &l) { return l.a32.p; }
   static const float *cf(LevelWork &l) { return l.cf32.p; }
+  static const float *res(const Level &L) { return L.res_c32.p; }
+  static const float *pro(const Level &L) { return L.pro_c32.p; }
   static float *sig(Workspace &w) { return w.sig32.p; }
   static float *one(Workspace &w) { return w.one32.p; }
 };
@@ -710,6 +726,7 @@ constexpr int kDefaultChebSmall = 9;
 constexpr int kDefaultChebConcurrent = 7;
 constexpr double kSmallBatchWork = 5e7;
 constexpr double kChebTwoRows = 50000.0;
+constexpr int64_t kCycMaxRows = 4096;  // more patch coefficients than any level that fits one block's LDS
 
 static std::string plan_key(const std::vector<double> &sig) {
   std::ostringstream os;
@@ -879,6 +896,65 @@ static int level_degree(const gf_space *sp, const SolveSpec &spec, int li) {
   return spec.cheb;
 }
 
+// Arguments of the V-cycle's part that runs as one launch (k_cycle.hip): levels 0 .. top, top the
+// largest below the space's finest that fits a block's LDS (top -1: none, the levels are launched one
+// by one).  Levels of that size take less time in the block than their launches do alone, at any number
+// of tiles: degree 3 (294 patch coefficients on level 2), FP32, 5 and 11 tiles: 51 and 52 us a cycle
+// against 235 and 290 us for the same steps launched one by one; 7 samples on 32 x 32 elements 11.22 ->
+// 9.61 ms, six requests on 32 x 32 28.1 -> 24.1 ms, 64 samples in FP64 on degree 2, 64 x 64 56.6 -> 54.8 ms.
+// (With only the dense solve in the launch: 10.2, 25.6 and 55.3 ms.)
+template <typename T>
+static CycleArgs<T> cycle_args(const gf_space *sp, Workspace &w, const SolveSpec &spec) {
+  CycleArgs<T> g;
+  g.top = -1;
+  if (spec.kind != GF_APPLY_STENCIL || sp->lev[0]->ngroups == 0) return g;
+  g.p = sp->p;
+  g.N0 = sp->N0;
+  g.ldb = w.ldb;
+  g.sig = Prec<T>::sig(w);
+  g.Ainv = spec.plan->Ainv.p;
+  g.node = w.node.p;
+  g.rgid = sp->lev[0]->row_gid.p;
+  g.active = w.active.p;
+  g.cs = w.cs.p;
+  for (int li = 0; li + 1 < sp->nlev() && li < kCycMaxLevels; ++li) {
+    const Level &L = *sp->lev[li];
+    LevelWork &lw = w.lw[li];
+    CycleArg<T> &c = g.lev[li];
+    if ((int64_t)L.npatch * L.n1 * L.n1 > kCycMaxRows) break;
+    c.n1 = L.n1;
+    c.nrow = L.npatch * L.n1 * L.n1;
+    c.deg = li > 0 ? level_degree(sp, spec, li) : 0;
+    c.ngroups = L.ngroups;
+    c.ncopies = L.ncopies;
+    c.stM = Prec<T>::stM(L);
+    c.stS = Prec<T>::stS(L);
+    c.dM = Prec<T>::dM(L);
+    c.dS = Prec<T>::dS(L);
+    c.cf = Prec<T>::cf(lw);
+    c.crow = L.crow.p;
+    c.cpos = L.cpos.p;
+    c.gp = L.grp_ptr.p;
+    c.gc = L.grp_coef.p;
+    c.r = Prec<T>::r(lw);
+    c.za = Prec<T>::za(lw);
+    c.zb = Prec<T>::zb(lw);
+    c.rw = L.rw;
+    c.pw = L.pw;
+    c.rs = L.res_start.p;
+    c.ps = L.pro_start.p;
+    c.rcoef = Prec<T>::res(L);
+    c.pcoef = Prec<T>::pro(L);
+    g.top = li;
+    if (!cycle_fits(cycle_layout(g))) {
+      g.top = li - 1;
+      break;
+    }
+  }
+  if (g.top >= 0) cycle_layout(g);
+  return g;
+}
+
 // Multigrid V-cycle on level li for the assembled right-hand side rsrc (type TR; converted to T into
 // rconv when the types differ).  Pre-smoothing: Chebyshev-Jacobi from zero; coarse correction with
 // the knot-insertion restriction of the residual, recursion, prolongation; post-smoothing with the
@@ -974,8 +1050,15 @@ static T *vcycle(gf_space *sp, Workspace &w, const SolveSpec &spec, int li, cons
   const Level &C = *sp->lev[li - 1];
   T *rc = Prec<T>::r(w.lw[li - 1]);
   restrict_residual<T>(L, C, rc, a, nullptr, ldb, nt, act, s);
-  launch_interface_sum<T>(C, rc, ldb, nt, act, s);
-  T *zc = vcycle<T, T>(sp, w, spec, li - 1, rc, nullptr, -1, nullptr, s);
+  T *zc;
+  const CycleArgs<T> cyc = cycle_args<T>(sp, w, spec);
+  if (li - 1 == cyc.top) {
+    coarse_cycle<T>(cyc, nt, w.rows16, s);
+    zc = cyc.top == 0 ? Prec<T>::za(w.lw[0]) : Prec<T>::zb(w.lw[cyc.top]);
+  } else {
+    launch_interface_sum<T>(C, rc, ldb, nt, act, s);
+    zc = vcycle<T, T>(sp, w, spec, li - 1, rc, nullptr, -1, nullptr, s);
+  }
   prolong_add<T>(L, C, za, zc, ldb, nt, act, s);
   // post-smoothing
   for (int k = 0; k < deg; ++k) smooth(k, k == deg - 1, 0);

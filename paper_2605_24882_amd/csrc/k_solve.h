@@ -208,6 +208,39 @@ void prolong_add(const Level &F, const Level &C, T *zf, const T *zc, int ldb, in
 template <typename T>
 void coarse_solve(const Level &C, int N0, T *z, const T *r, const double *Ainv, const int *node, int ldb, int ntiles,
                   const int *active, hipStream_t s);
+// the V-cycle's coarsest levels in one launch (k_cycle.hip): one level's data ...
+constexpr int kCycMaxLevels = 8;
+template <typename T>
+struct CycleArg {
+  int n1 = 0, nrow = 0, deg = 0, ngroups = 0, ncopies = 0, rw = 0, pw = 0;
+  int o_row = 0, o_pos = 0, o_dM = 0, o_dS = 0, o_gp = 0, o_gc = 0, o_rs = 0, o_rc = 0, o_ps = 0, o_pc = 0;
+  const T *stM = nullptr, *stS = nullptr, *dM = nullptr, *dS = nullptr, *cf = nullptr;
+  // patch coefficients in order: padded row, position among the copies of shared unknowns or -1; the
+  // copies (CSR) as patch coefficients
+  const int *crow = nullptr, *cpos = nullptr, *gp = nullptr, *gc = nullptr;
+  T *r = nullptr, *za = nullptr, *zb = nullptr;
+  // transfers to and from the next coarser level
+  const int *rs = nullptr, *ps = nullptr;
+  const T *rcoef = nullptr, *pcoef = nullptr;
+};
+// ... and the launch: levels 0 .. top, lev[top].r holding the restricted residual (patch contributions);
+// the result is left in lev[top].zb (za when top is 0)
+template <typename T>
+struct CycleArgs {
+  int top = 0, p = 0, N0 = 0, n0r = 0, ncb = 0, nrow = 0, o_gid = 0;
+  int64_t ldb = 0;
+  size_t lds = 0;
+  const T *sig = nullptr;
+  const double *Ainv = nullptr;
+  const int *node = nullptr, *rgid = nullptr, *active = nullptr;
+  const ColState *cs = nullptr;
+  CycleArg<T> lev[kCycMaxLevels];
+};
+template <typename T>
+size_t cycle_layout(CycleArgs<T> &g);  // fills the offsets, returns the LDS bytes
+bool cycle_fits(size_t lds);
+template <typename T>
+void coarse_cycle(const CycleArgs<T> &g, int ntiles, bool same16, hipStream_t s);
 void global_to_local(const Level &L, double *X, const double *src, int nvec, int ldb, hipStream_t s);
 void local_to_global(const Level &L, double *dst, const double *X, int nvec, int c0, int ldb, hipStream_t s);
 // Y[r][c] = X[r][c mod S] for c < K S and 0 up to column ncw (ncw < 0: the whole row, ldy columns);
