@@ -39,6 +39,59 @@ void hip_check(hipError_t e, const char *what, const char *file, int line) {
   fail(e == hipErrorOutOfMemory ? GF_ENOMEM : GF_EDEVICE, os.str());
 }
 
+void *Pool::take(size_t bytes, size_t *got) {
+  const size_t want = (bytes + 255) / 256 * 256;
+  {
+    std::lock_guard<std::mutex> lk(mu_);
+    // the smallest block that is large enough and wastes at most a quarter
+    auto best = free_.end();
+    for (auto it = free_.begin(); it != free_.end(); ++it)
+      if (it->bytes >= want && it->bytes <= want + want / 4 + 4096 && (best == free_.end() || it->bytes < best->bytes))
+        best = it;
+    if (best != free_.end()) {
+      void *p = best->p;
+      *got = best->bytes;
+      held_ -= best->bytes;
+      free_.erase(best);
+      return p;
+    }
+  }
+  void *p = nullptr;
+  hipError_t e = hipMalloc(&p, want);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      trim(0);
+    }
+    e = hipMalloc(&p, want);
+  }
+  HIPCHK(e);
+  *got = want;
+  return p;
+}
+void Pool::give(void *p, size_t bytes) {
+  try {
+    if (bytes <= kPoolBytes / 2) {  // (a larger block would push out all the others)
+      std::lock_guard<std::mutex> lk(mu_);
+      free_.push_back({p, bytes});
+      held_ += bytes;
+      trim(kPoolBytes);
+      return;
+    }
+  } catch (...) {  // no host memory for the list entry
+  }
+  (void)hipFree(p);
+}
+void Pool::trim(size_t bound) {
+  while (held_ > bound && !free_.empty()) {
+    held_ -= free_.front().bytes;
+    (void)hipFree(free_.front().p);
+    free_.pop_front();
+  }
+}
+Pool::~Pool() { trim(0); }
+
 template <class F>
 static gf_status guarded(F &&f) {
   try {
@@ -283,13 +336,15 @@ struct Plan {
   uint64_t last = 0;                      // the space's call that used it last
 };
 
+constexpr int kMaxCheb = 16;  // the most smoothing steps a caller may ask for
+
 struct LevelWork {
   DBuf<double> r64, z64a, z64b, a64;  // V-cycle vectors (FP64 mode)
   DBuf<float> r32, z32a, z32b, a32;   // V-cycle vectors (mixed mode)
   // Chebyshev coefficients per step and system, [2][deg][ldb]: c1 of step k at k ldb, c2 / b_max of
   // step k at (deg + k) ldb
-  DBuf<double> cf64;
-  DBuf<float> cf32;
+  DView<double> cf64;
+  DView<float> cf32;
 };
 
 // Event pairs around the finest-level smoothing launches of one batch (GF_FLAG_TIME_APPLY), each
@@ -321,9 +376,16 @@ struct Workspace {
   // mixed precision: the search direction stored in FP32 (see BatchSolve::p32)
   DBuf<float> p32;
   std::vector<LevelWork> lw;
-  DBuf<double> sig64, one64, zero64;
-  DBuf<float> sig32, one32;
-  DBuf<int> node, active;
+  DBuf<double> one64, zero64;
+  DBuf<float> one32;
+  // what a batch sets per column (shifts, nodes, CG state, active tiles, smoothing coefficients): parts of
+  // one device block that prepare() fills with one copy
+  DBuf<char> stage;
+  size_t cf_off = 0;  // where the smoothing coefficients start, levels 1, 2, ... in order
+  DView<double> sig64;
+  DView<float> sig32;
+  DView<int> node, active;
+  DBuf<double> Ainv;  // the plan's coarse inverses, copied: captured graphs refer to the workspace only
   // outer-CG fusion: while set, the finest level's first smoothing step also performs r -= alpha q
   // (q = fuse_q) and the convergence test, and records the tiles active before it in active0
   const double *fuse_q = nullptr;
@@ -331,7 +393,7 @@ struct Workspace {
   // (the reference of the convergence test, at the start of a solve)
   bool fuse_bb = false;
   DBuf<int> active0;
-  DBuf<ColState> cs;
+  DView<ColState> cs;
   DBuf<double> partial;
   int ncols = 0;  // columns of the current batch (the rest of ldb pads the last tile)
   std::vector<int> active_h;
@@ -357,8 +419,8 @@ struct gf_tape {
   double bf = 0;
   std::vector<double> node_sig, omega;
   int passes = 1;                       // applications of the rule (2 for an improved split)
-  std::vector<gf::DBuf<double>> xk;     // per pass: [R][ldf] node solutions, column k*nsamp + s
-  std::vector<gf::DBuf<double>> w;      // w[i-1]: [R][ldc] chain solution w_i
+  std::vector<gf::PBuf<double>> xk;     // per pass: [R][ldf] node solutions, column k*nsamp + s
+  std::vector<gf::PBuf<double>> w;      // w[i-1]: [R][ldc] chain solution w_i
 };
 
 namespace gf {
@@ -415,15 +477,33 @@ static Workspace &get_workspace(gf_space *sp, int ldb, int prec, int slot = 0) {
       v.a32.alloc(n);
     }
   }
-  w->sig64.alloc(ldb);
   w->one64.alloc(ldb);
   w->zero64.alloc(ldb);
-  w->sig32.alloc(ldb);
   w->one32.alloc(ldb);
-  w->node.alloc(ldb);
-  w->active.alloc(w->ntiles);
   w->active0.alloc(w->ntiles);
-  w->cs.alloc(ldb);
+  // the block of per-column data; coarser levels take at most two smoothing steps, the finest kMaxCheb
+  const size_t elem = prec == GF_PREC_FP64 ? sizeof(double) : sizeof(float);
+  size_t off = 0;
+  auto part = [&](size_t bytes) {
+    const size_t o = off;
+    off += (bytes + 255) / 256 * 256;
+    return o;
+  };
+  const size_t o_cs = part(ldb * sizeof(ColState)), o_s64 = part(ldb * sizeof(double)), o_s32 = part(ldb * sizeof(float)),
+               o_node = part(ldb * sizeof(int)), o_act = part(w->ntiles * sizeof(int));
+  w->cf_off = off;
+  std::vector<size_t> o_cf(sp->nlev(), 0);
+  for (int li = 1; li < sp->nlev(); ++li) o_cf[li] = part(2 * (li + 1 < sp->nlev() ? 2 : kMaxCheb) * (size_t)ldb * elem);
+  w->stage.alloc(off);
+  w->cs.p = reinterpret_cast<ColState *>(w->stage.p + o_cs);
+  w->sig64.p = reinterpret_cast<double *>(w->stage.p + o_s64);
+  w->sig32.p = reinterpret_cast<float *>(w->stage.p + o_s32);
+  w->node.p = reinterpret_cast<int *>(w->stage.p + o_node);
+  w->active.p = reinterpret_cast<int *>(w->stage.p + o_act);
+  for (int li = 1; li < sp->nlev(); ++li) {
+    if (prec == GF_PREC_FP64) w->lw[li].cf64.p = reinterpret_cast<double *>(w->stage.p + o_cf[li]);
+    else w->lw[li].cf32.p = reinterpret_cast<float *>(w->stage.p + o_cf[li]);
+  }
   w->partial.alloc(scratch_slots(sp, ldb, w->ntiles) * ldb);
   std::vector<double> ones(ldb, 1.0);
   std::vector<float> onesf(ldb, 1.0f);
@@ -748,14 +828,15 @@ static Plan &get_plan(gf_space *sp, const std::vector<double> &sig) {
   pl->sig = sig;
   const int nn = (int)sig.size();
   const int ldb = round_up(nn, CT), nt = ldb / CT;
-  DBuf<double> dsig, one, v, w, v2, out;
+  const std::shared_ptr<Pool> &pool = sp->ctx->pool;
+  PBuf<double> dsig, one, v, w, v2, out;
   std::vector<double> hsig(ldb, 1.0), ones(ldb, 1.0);
   for (int k = 0; k < nn; ++k) hsig[k] = sig[k];
-  dsig.upload(hsig, s);
-  one.upload(ones, s);
-  DBuf<double> partial;
-  partial.alloc((size_t)2 * kMaxRowBlocks * ldb);
-  out.alloc((size_t)2 * ldb);
+  dsig.upload(pool, hsig, s);
+  one.upload(pool, ones, s);
+  PBuf<double> partial;
+  partial.alloc(pool, (size_t)2 * kMaxRowBlocks * ldb);
+  out.alloc(pool, (size_t)2 * ldb);
   Scratch sc{partial.p};
   pl->invb.assign(sp->nlev(), std::vector<double>(nn, 0.0));
   pl->mshare.assign(sp->nlev(), std::vector<double>(nn, 0.0));
@@ -763,14 +844,14 @@ static Plan &get_plan(gf_space *sp, const std::vector<double> &sig) {
   for (int li = 1; li < sp->nlev(); ++li) {
     const Level &L = *sp->lev[li];
     const size_t n = (size_t)L.R * ldb;
-    v.alloc(n);
-    w.alloc(n);
-    v2.alloc(n);
+    v.alloc_zero(pool, n, s);  // (ghost rows of the iterates are read)
+    w.alloc(pool, n);
+    v2.alloc_zero(pool, n, s);
     hash_fill(L, v.p, ldb, nt, s);
     for (int itp = 0; itp < kPowerIters; ++itp) {
       apply_level<double>(L, GF_APPLY_STENCIL, v.p, w.p, dsig.p, one.p, ldb, nt, nullptr, s, false);
       div_diag(L, v2.p, w.p, dsig.p, ldb, nt, s);
-      if (itp + 1 < kPowerIters) std::swap(v.p, v2.p);
+      if (itp + 1 < kPowerIters) std::swap(v, v2);
     }
     // lambda ~ (w . v_{k+1}) / (w . v_k) with w = A v_k, v_{k+1} = D^-1 w
     reduce_dot2<double, double, double>(L, v.p, w.p, v2.p, sc, ldb, nt, nullptr, nullptr, OP_STORE, 0.0, 0,
@@ -789,12 +870,12 @@ static Plan &get_plan(gf_space *sp, const std::vector<double> &sig) {
     v2.release();
   }
   // coarse factors
-  DBuf<double> sn;
-  sn.upload(sig, s);
-  DBuf<double> Lf;
-  Lf.alloc((size_t)nn * sp->N0 * sp->N0);
-  DBuf<int> info;
-  info.alloc(nn);
+  PBuf<double> sn;
+  sn.upload(pool, sig, s);
+  PBuf<double> Lf;
+  Lf.alloc(pool, (size_t)nn * sp->N0 * sp->N0);
+  PBuf<int> info;
+  info.alloc(pool, nn);
   launch_coarse_factor(sp->M0.p, sp->S0.p, sp->N0, sn.p, nn, Lf.p, info.p, s);
   std::vector<int> hinfo(nn);
   HIPCHK(hipMemcpyAsync(hinfo.data(), info.p, nn * sizeof(int), hipMemcpyDeviceToHost, s));
@@ -912,7 +993,7 @@ static CycleArgs<T> cycle_args(const gf_space *sp, Workspace &w, const SolveSpec
   g.N0 = sp->N0;
   g.ldb = w.ldb;
   g.sig = Prec<T>::sig(w);
-  g.Ainv = spec.plan->Ainv.p;
+  g.Ainv = w.Ainv.p;
   g.node = w.node.p;
   g.rgid = sp->lev[0]->row_gid.p;
   g.active = w.active.p;
@@ -976,7 +1057,7 @@ static T *vcycle(gf_space *sp, Workspace &w, const SolveSpec &spec, int li, cons
       convert_rows<TR, T>(L, rsrc, rconv, ldb, nt, act, s);
       r = rconv;
     }
-    coarse_solve<T>(L, sp->N0, za, r, spec.plan->Ainv.p, w.node.p, ldb, nt, act, s);
+    coarse_solve<T>(L, sp->N0, za, r, w.Ainv.p, w.node.p, ldb, nt, act, s);
     return za;
   }
   const T *r = rconv ? (const T *)rconv : (const T *)rsrc;
@@ -1087,7 +1168,7 @@ static T *bpx(gf_space *sp, Workspace &w, const SolveSpec &spec, const TR *rsrc,
     launch_interface_sum<T>(C, rc, ldb, nt, act, s);
   }
   T *zc = Prec<T>::za(w.lw[0]);
-  coarse_solve<T>(*sp->lev[0], sp->N0, zc, Prec<T>::r(w.lw[0]), spec.plan->Ainv.p, w.node.p, ldb, nt, act, s);
+  coarse_solve<T>(*sp->lev[0], sp->N0, zc, Prec<T>::r(w.lw[0]), w.Ainv.p, w.node.p, ldb, nt, act, s);
   for (int l = 1; l <= fi; ++l) {
     const Level &L = *sp->lev[l], &C = *sp->lev[l - 1];
     T *z = Prec<T>::za(w.lw[l]);
@@ -1132,52 +1213,67 @@ struct BatchSolve {
       spec.cheb = concurrent > 1 ? kDefaultChebConcurrent
                   : ((double)spec.ncols * F.N < kSmallBatchWork || spec.rough_load) ? kDefaultChebSmall
                                                                                      : kDefaultCheb;
-    std::vector<double> sig(ldb, 1.0);
-    std::vector<float> sigf(ldb, 1.0f);
-    std::vector<int> node(ldb, 0);
-    std::vector<ColState> cs(ldb);
+    // everything per column, laid out as the workspace's block and copied at once
+    const char *base = w->stage.p;
+    std::vector<char> h(w->stage.n, 0);
+    auto at = [&](const void *dev) { return h.data() + (static_cast<const char *>(dev) - base); };
+    double *sig = reinterpret_cast<double *>(at(w->sig64.p));
+    float *sigf = reinterpret_cast<float *>(at(w->sig32.p));
+    int *node = reinterpret_cast<int *>(at(w->node.p)), *act = reinterpret_cast<int *>(at(w->active.p));
+    ColState *cs = reinterpret_cast<ColState *>(at(w->cs.p));
     for (int c = 0; c < ldb; ++c) {
       cs[c] = ColState{};
       cs[c].done = (c < spec.ncols) ? 0 : 1;
-      if (c < spec.ncols) {
-        sig[c] = spec.col_sig[c];
-        node[c] = spec.col_node[c];
-      }
+      sig[c] = c < spec.ncols ? spec.col_sig[c] : 1.0;
+      node[c] = c < spec.ncols ? spec.col_node[c] : 0;
       sigf[c] = (float)sig[c];
     }
     std::fill(w->active_h.begin(), w->active_h.end(), 0);
     for (int c = 0; c < spec.ncols; ++c) w->active_h[c / CT] = 1;
+    std::copy(w->active_h.begin(), w->active_h.end(), act);
     // shift structure of the column tiles (padding columns carry the shift 1)
     w->nslot = 0;
     w->rows16 = 1;
     for (int t = 0; t < w->ntiles; ++t) {
       std::vector<double> d;
       for (int c = t * CT; c < (t + 1) * CT; ++c) {
-        if (std::find(d.begin(), d.end(), sig[c]) == d.end()) d.push_back(sig[c]);
+        if ((c == t * CT || sig[c] != sig[c - 1]) && std::find(d.begin(), d.end(), sig[c]) == d.end())
+          d.push_back(sig[c]);
         if (c % 16 != 0 && sig[c] != sig[c - 1]) w->rows16 = 0;
       }
       w->nslot = std::max(w->nslot, (int)d.size());
     }
-    w->sig64.upload(sig, s);
-    w->sig32.upload(sigf, s);
-    w->node.upload(node, s);
-    w->cs.upload(cs, s);
-    w->active.upload(w->active_h, s);
     // Chebyshev coefficients of every smoothing step per system (the interval depends on the node)
-    for (int li = 1; li < sp->nlev() && !spec.mass_shift; ++li) {
+    size_t used = w->cf_off;
+    for (int li = 1; li < sp->nlev() && !spec.mass_shift && spec.precond == GF_PRECOND_VCYCLE; ++li) {
       const int deg = level_degree(sp, spec, li);
-      std::vector<double> cf((size_t)2 * deg * ldb, 0.0), c1, c2;
-      for (int c = 0; c < spec.ncols; ++c) {
-        const int k = node[c];
+      const int nn = (int)spec.plan->sig.size();
+      std::vector<double> k1((size_t)nn * deg), k2((size_t)nn * deg), c1, c2;
+      for (int k = 0; k < nn; ++k) {
         cheb_coeffs(deg, spec.smooth_load ? 1.0 / kChebAlpha : interval_ia(*spec.plan, li, k, deg), c1, c2);
         for (int st = 0; st < deg; ++st) {
-          cf[(size_t)st * ldb + c] = c1[st];
-          cf[(size_t)(deg + st) * ldb + c] = c2[st] * spec.plan->invb[li][k];
+          k1[(size_t)k * deg + st] = c1[st];
+          k2[(size_t)k * deg + st] = c2[st] * spec.plan->invb[li][k];
         }
       }
-      std::vector<float> cff(cf.begin(), cf.end());
-      w->lw[li].cf64.upload(cf, s);
-      w->lw[li].cf32.upload(cff, s);
+      auto fill = [&](auto *cf) {
+        using T = std::remove_pointer_t<decltype(cf)>;
+        for (int st = 0; st < deg; ++st)
+          for (int c = 0; c < spec.ncols; ++c) {
+            cf[(size_t)st * ldb + c] = (T)k1[(size_t)node[c] * deg + st];
+            cf[(size_t)(deg + st) * ldb + c] = (T)k2[(size_t)node[c] * deg + st];
+          }
+        used = (size_t)(reinterpret_cast<char *>(cf + (size_t)2 * deg * ldb) - h.data());
+      };
+      if (mixed()) fill(reinterpret_cast<float *>(at(w->lw[li].cf32.p)));
+      else fill(reinterpret_cast<double *>(at(w->lw[li].cf64.p)));
+    }
+    HIPCHK(hipMemcpyAsync(w->stage.p, h.data(), used, hipMemcpyHostToDevice, s));
+    HIPCHK(hipStreamSynchronize(s));  // before h goes
+    if (spec.plan) {
+      const size_t na = spec.plan->Ainv.n;
+      if (w->Ainv.n < na) w->Ainv.alloc(na);
+      HIPCHK(hipMemcpyAsync(w->Ainv.p, spec.plan->Ainv.p, na * sizeof(double), hipMemcpyDeviceToDevice, s));
     }
     HIPCHK(hipMemsetAsync(w->x.p, 0, (size_t)F.R * ldb * sizeof(double), s));
   }
@@ -1412,7 +1508,8 @@ constexpr int kGraphChunk = 4;    // CG iterations per captured graph
 constexpr size_t kMaxGraphs = 32;  // instantiated graphs kept per context
 
 // Identity of a captured chunk: everything its kernels take as arguments -- the batches' spaces,
-// plans, workspaces and their buffers, and the solver settings baked into the launches.
+// workspaces and their buffers, and the solver settings baked into the launches.  What depends on the
+// shifts lies in workspace buffers that prepare() fills, so batches of the same shape share a graph.
 static std::string graph_key(const std::vector<BatchSolve *> &items, int chunk) {
   std::ostringstream os;
   os.precision(17);
@@ -1420,13 +1517,13 @@ static std::string graph_key(const std::vector<BatchSolve *> &items, int chunk) 
   for (const BatchSolve *it : items) {
     const Workspace &w = *it->w;
     const SolveSpec &sp = it->spec;
-    os << "|" << (const void *)it->sp << "," << (const void *)sp.plan << "," << (const void *)&w << "," << w.ldb
+    os << "|" << (const void *)it->sp << "," << (const void *)&w << "," << w.ldb
        << "," << sp.prec << "," << sp.kind << "," << sp.cheb << "," << sp.rtol << "," << sp.max_iter << ","
        << sp.flags << "," << w.ncols << "," << sp.precond << "," << sp.mass_shift << "," << sp.smooth_load << "," << w.nslot << ","
        << w.rows16 << "," << it->p32 << "," << (const void *)w.x.p << "," << (const void *)w.r.p << ","
        << (const void *)w.p.p << "," << (const void *)w.p32.p << "," << (const void *)w.q.p << "," << (const void *)w.cs.p << "," << (const void *)w.partial.p << ","
        << (const void *)w.active.p << "," << (const void *)w.sig64.p;
-    if (sp.plan) os << "," << (const void *)sp.plan->Ainv.p;
+    os << "," << (const void *)w.Ainv.p;
     for (const LevelWork &l : w.lw)
       os << "," << (const void *)l.z64a.p << (const void *)l.z32a.p << (const void *)l.cf64.p << (const void *)l.cf32.p;
   }
@@ -1519,9 +1616,11 @@ static void begin_call(gf_space *sp) {
 // Smoothing degree of a batch solved alone with at least kTuneMinWork columns x unknowns (the caller
 // leaving the degree to the library): on its first solve the batch is solved once with every
 // candidate degree, eagerly from its own right-hand side, and timed with HIP events to convergence;
-// the fastest degree is kept for the space and the batch configuration (shifts, width, precision,
-// tolerance, load), so later calls with the same batch reuse it.  The right-hand side is restored
-// before the solve proper.  (Predicting the iteration count from the residual reduction of the first
+// the fastest degree is kept for the space and the batch configuration (number of shifts and the powers
+// of two of their extremes, width, precision, tolerance, load), so later calls with such a batch reuse
+// it -- also when kappa differs in every call, as in a fit of kappa: tuning for the exact shifts
+// took five of the six solves of every step there (degree 3, 64 x 64, 16 samples: 301 -> 54 ms a step).  The
+// right-hand side is restored before the solve proper.  (Predicting the iteration count from the residual reduction of the first
 // few iterations favoured high degrees that were slower to convergence.)  A batch below
 // kSmallBatchWork (one column tile on a large mesh, such as a step of the integer chain) is bound by
 // latency rather than memory traffic, and its candidates reach the high degrees that cut the
@@ -1542,8 +1641,10 @@ static void tune_degree(hipStream_t s, BatchSolve &b) {
   std::ostringstream key;
   key.precision(17);
   key << b.w->ldb << "," << sp0.ncols << "," << sp0.prec << "," << sp0.rtol << "," << sp0.max_iter << ","
-      << sp0.rough_load << "," << sp0.smooth_load << "," << plan_key(sp0.plan->sig) << "|";
-  for (int c = 0; c < sp0.ncols; ++c) key << sp0.col_node[c] << ",";
+      << sp0.rough_load << "," << sp0.smooth_load << "," << sp0.plan->sig.size();
+  // the shifts by their extremes' powers of two
+  const auto mm = std::minmax_element(sp0.plan->sig.begin(), sp0.plan->sig.end());
+  key << "," << std::ilogb(*mm.first) << "," << std::ilogb(*mm.second);
   auto it = b.sp->cheb_tuned.find(key.str());
   if (it == b.sp->cheb_tuned.end()) {
     const size_t nr = (size_t)F.R * b.w->ldb;
@@ -1805,6 +1906,7 @@ gf_status gf_context_create(int32_t device, void *hip_stream, gf_context **out) 
     noalloc_register(device);
     std::unique_ptr<gf_context> c(new gf_context());
     c->device = device;
+    c->pool = std::make_shared<Pool>();
     c->stream = (hipStream_t)hip_stream;  // NULL: the device's null stream
     *out = c.release();
   });
@@ -2013,13 +2115,13 @@ gf_status gf_space_dofmap(const gf_space *sp, int32_t *l2g) {
 // device copy of a caller array (or the caller's device pointer itself)
 struct InArray {
   const double *p = nullptr;
-  DBuf<double> own;
+  PBuf<double> own;
 };
-static void stage_in(InArray &a, const double *src, size_t n, int mem, hipStream_t s) {
+static void stage_in(const gf_context *ctx, InArray &a, const double *src, size_t n, int mem, hipStream_t s) {
   if (mem == GF_DEVICE) {
     a.p = src;
   } else {
-    a.own.upload(src, n, s);
+    a.own.upload(ctx->pool, src, n, s);
     a.p = a.own.p;
   }
 }
@@ -2027,14 +2129,14 @@ struct OutArray {
   double *p = nullptr;
   double *host = nullptr;
   size_t n = 0;
-  DBuf<double> own;
+  PBuf<double> own;
 };
-static void stage_out(OutArray &a, double *dst, size_t n, int mem) {
+static void stage_out(const gf_context *ctx, OutArray &a, double *dst, size_t n, int mem) {
   a.n = n;
   if (mem == GF_DEVICE) {
     a.p = dst;
   } else {
-    a.own.alloc(n);
+    a.own.alloc(ctx->pool, n);
     a.p = a.own.p;
     a.host = dst;
   }
@@ -2058,15 +2160,17 @@ gf_status gf_space_apply(const gf_space *csp, double sigma, double s_scale, int3
     const Level &F = sp->fine();
     const size_t n = (size_t)nvec * F.N;
     InArray xin;
-    stage_in(xin, x, n, mem, s);
+    stage_in(sp->ctx, xin, x, n, mem, s);
     OutArray yout;
-    stage_out(yout, y, n, mem);
+    stage_out(sp->ctx, yout, y, n, mem);
     const int ldb = round_up(nvec, CT), nt = ldb / CT;
-    DBuf<double> X, Y, ca, cb;
-    X.alloc((size_t)F.R * ldb);
-    Y.alloc((size_t)F.R * ldb);
-    ca.upload(std::vector<double>(ldb, sigma), s);
-    cb.upload(std::vector<double>(ldb, s_scale), s);
+    PBuf<double> X, Y, ca, cb;
+    X.alloc(sp->ctx->pool, (size_t)F.R * ldb);
+    Y.alloc(sp->ctx->pool, (size_t)F.R * ldb);
+    ca.alloc(sp->ctx->pool, ldb);
+    cb.alloc(sp->ctx->pool, ldb);
+    hipLaunchKernelGGL(k_fill2, dim3((ldb + 255) / 256), dim3(256), 0, s, ca.p, sigma, cb.p, s_scale, ldb);
+    HIPCHK(hipGetLastError());
     global_to_local(F, X.p, xin.p, nvec, ldb, s);
     apply_level<double>(F, kind, X.p, Y.p, ca.p, cb.p, ldb, nt, nullptr, s);
     local_to_global(F, yout.p, Y.p, nvec, 0, ldb, s);
@@ -2135,13 +2239,13 @@ gf_status gf_space_transfer(const gf_space *csp, int32_t level, int32_t directio
     const Level &F = *sp->lev[li], &C = *sp->lev[li - 1];
     const Level &In = direction == GF_PROLONG ? C : F, &Out = direction == GF_PROLONG ? F : C;
     InArray xin;
-    stage_in(xin, x, (size_t)nvec * In.N, mem, s);
+    stage_in(sp->ctx, xin, x, (size_t)nvec * In.N, mem, s);
     OutArray yout;
-    stage_out(yout, y, (size_t)nvec * Out.N, mem);
+    stage_out(sp->ctx, yout, y, (size_t)nvec * Out.N, mem);
     const int ldb = round_up(nvec, CT), nt = ldb / CT;
-    DBuf<double> XL, YL;  // patch-local layouts, zero-filled (ghost rows stay zero)
-    XL.alloc((size_t)In.R * ldb);
-    YL.alloc((size_t)Out.R * ldb);
+    PBuf<double> XL, YL;  // patch-local layouts; the prolongation adds to its output
+    XL.alloc(sp->ctx->pool, (size_t)In.R * ldb);
+    YL.alloc_zero(sp->ctx->pool, (size_t)Out.R * ldb, s);
     global_to_local(In, XL.p, xin.p, nvec, ldb, s);  // every copy of an unknown holds its value
     if (direction == GF_PROLONG) {
       prolong_add<double>(F, C, YL.p, XL.p, ldb, nt, nullptr, s);
@@ -2186,13 +2290,13 @@ gf_status gf_white_noise(const gf_space *csp, int32_t nsamp, const double *z, do
     const Level &F = sp->fine();
     const size_t nz = (size_t)nsamp * gf_space_noise_length(sp);
     InArray zin;
-    stage_in(zin, z, nz, mem, s);
+    stage_in(sp->ctx, zin, z, nz, mem, s);
     OutArray bout;
-    stage_out(bout, b, (size_t)nsamp * F.N, mem);
-    DBuf<double> ye, BL;
-    ye.alloc(nz);
+    stage_out(sp->ctx, bout, b, (size_t)nsamp * F.N, mem);
+    PBuf<double> ye, BL;
+    ye.alloc(sp->ctx->pool, nz);
     const int ldb = round_up(nsamp, CT);
-    BL.alloc((size_t)F.R * ldb);
+    BL.alloc(sp->ctx->pool, (size_t)F.R * ldb);
     launch_white_noise(F, zin.p, nsamp, ye.p, BL.p, ldb, s);
     // interface sum of the per-patch contributions, then owner copies out
     launch_interface_sum<double>(F, BL.p, ldb, ldb / CT, nullptr, s);
@@ -2212,7 +2316,7 @@ static void check_common(gf_space *sp, double kappa, double beta, const gf_quad_
   if (opts->precision != GF_PREC_FP64 && opts->precision != GF_PREC_MIXED) fail(GF_EINVAL, "unknown precision");
   if (!(opts->rtol > 0.0) || !(opts->rtol < 1.0)) fail(GF_EINVAL, "rtol must be in (0, 1)");
   if (opts->max_iter < 1) fail(GF_EINVAL, "max_iter must be >= 1");
-  if (opts->cheb_degree < 0 || opts->cheb_degree > 16) fail(GF_EINVAL, "cheb_degree must be in 0..16");
+  if (opts->cheb_degree < 0 || opts->cheb_degree > kMaxCheb) fail(GF_EINVAL, "cheb_degree must be in 0..16");
   if (opts->apply_kind != GF_APPLY_STENCIL && opts->apply_kind != GF_APPLY_SUMFACT)
     fail(GF_EINVAL, "unknown apply_kind");
   if (opts->preconditioner != GF_PRECOND_VCYCLE && opts->preconditioner != GF_PRECOND_BPX)
@@ -2260,7 +2364,7 @@ struct SampleItem {
   const Plan *chain_plan = nullptr, *frac_plan = nullptr;
   InArray bin;
   OutArray uout;
-  DBuf<double> rloc;
+  PBuf<double> rloc;
   Workspace *wc = nullptr, *wf = nullptr;
 };
 
@@ -2361,8 +2465,8 @@ static void run_items(gf_context *ctx, std::vector<SampleItem> &items, const gf_
   }
   for (auto &it : items) {
     const size_t nv = (size_t)it.nsamp * it.sp->fine().N;
-    stage_in(it.bin, it.b, nv, mem, s);
-    stage_out(it.uout, it.u, nv, mem);
+    stage_in(ctx, it.bin, it.b, nv, mem, s);
+    stage_out(ctx, it.uout, it.u, nv, mem);
   }
   hipEvent_t t0, t1;
   HIPCHK(hipEventCreate(&t0));
@@ -2424,8 +2528,8 @@ static void run_items(gf_context *ctx, std::vector<SampleItem> &items, const gf_
       const Level &F = it.sp->fine();
       const int ldc = it.wc->ldb;
       if (it.tape) {
-        DBuf<double> &dst = it.tape->w[i - 1];
-        dst.alloc((size_t)F.R * ldc);
+        PBuf<double> &dst = it.tape->w[i - 1];
+        dst.alloc(ctx->pool, (size_t)F.R * ldc);
         HIPCHK(hipMemcpyAsync(dst.p, it.wc->x.p, (size_t)F.R * ldc * sizeof(double), hipMemcpyDeviceToDevice, s));
       }
       if (i < it.n || it.bf > 0.0)  // next right-hand side M w_i (assembled)
@@ -2470,7 +2574,7 @@ static void run_items(gf_context *ctx, std::vector<SampleItem> &items, const gf_
           rsrc = it.wc->r.p;
           ldr = it.wc->ldb;
         } else {
-          it.rloc.alloc((size_t)F.R * ldc);
+          it.rloc.alloc(ctx->pool, (size_t)F.R * ldc);
           global_to_local(F, it.rloc.p, it.bin.p, it.nsamp, ldc, s);
           rsrc = it.rloc.p;
           ldr = ldc;
@@ -2506,25 +2610,23 @@ static void run_items(gf_context *ctx, std::vector<SampleItem> &items, const gf_
         if (it.tape) {  // alone in its group: the node solutions start at column 0
           const size_t nx = (size_t)F.R * it.wf->ldb;
           if ((int)it.tape->xk.size() < it.passes) it.tape->xk.resize(it.passes);
-          it.tape->xk[pass].alloc(nx);
+          it.tape->xk[pass].alloc(ctx->pool, nx);
           HIPCHK(hipMemcpyAsync(it.tape->xk[pass].p, it.wf->x.p, nx * sizeof(double), hipMemcpyDeviceToDevice, s));
         }
-        DBuf<double> om;
-        om.upload(it.omega, s);
+        PBuf<double> om;
+        om.upload(ctx->pool, it.omega, s);
         // the sum lands in u; before a further pass it becomes that pass's right-hand side M u
         quadrature_sum(F, it.uout.p, it.wf->x.p + gr.off[m], om.p, (int)it.omega.size(), it.nsamp, it.wf->ldb, s);
         if (pass + 1 < it.passes) {
           const int ldc = round_up(it.nsamp, CT);
-          DBuf<double> vloc;
-          vloc.alloc((size_t)F.R * ldc);
+          PBuf<double> vloc;
+          vloc.alloc(ctx->pool, (size_t)F.R * ldc);
           global_to_local(F, vloc.p, it.uout.p, it.nsamp, ldc, s);
-          it.rloc.alloc((size_t)F.R * ldc);
+          it.rloc.alloc_zero(ctx->pool, (size_t)F.R * ldc, s);  // (its ghost rows go into the batch)
           Workspace &wv = *it.wf;
           apply_level<double>(F, GF_APPLY_STENCIL, vloc.p, it.rloc.p, wv.one64.p, wv.zero64.p, ldc, ldc / CT, nullptr,
                               s);
-          HIPCHK(hipStreamSynchronize(s));  // before vloc is released
         }
-        HIPCHK(hipStreamSynchronize(s));
       }
     }
   }
@@ -2591,18 +2693,20 @@ static void run_grad(gf_tape &t, const double *g_in, double *grad, int mem, gf_s
       setup_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - c0).count();
   }
   InArray gin;
-  stage_in(gin, g_in, (size_t)nsamp * F.N, mem, s);
+  stage_in(sp->ctx, gin, g_in, (size_t)nsamp * F.N, mem, s);
   OutArray gout;
-  stage_out(gout, grad, (size_t)nsamp, mem);
+  stage_out(sp->ctx, gout, grad, (size_t)nsamp, mem);
   hipEvent_t t0, t1;
   HIPCHK(hipEventCreate(&t0));
   HIPCHK(hipEventCreate(&t1));
   HIPCHK(hipEventRecord(t0, s));
   const int64_t sync0 = ctx->host_syncs;
-  DBuf<double> acc, dots, one;
-  acc.alloc(nsamp);
-  dots.alloc((size_t)2 * std::max(t.ldf, t.ldc));
-  one.upload(std::vector<double>{1.0}, s);
+  const std::shared_ptr<Pool> &pool = ctx->pool;
+  PBuf<double> acc, dots, one;
+  acc.alloc_zero(pool, nsamp, s);
+  dots.alloc(pool, (size_t)2 * std::max(t.ldf, t.ldc));
+  const std::vector<double> h_one{1.0};
+  one.upload(pool, h_one, s);
   SolveResult tot;
   int nsys = 0;
   auto account = [&](const BatchSolve &b) {
@@ -2623,10 +2727,10 @@ static void run_grad(gf_tape &t, const double *g_in, double *grad, int mem, gf_s
     // the passes of the rule backwards: the last pass takes dL/du; each earlier pass takes M times
     // the weighted sum mu of the later pass's adjoint solutions
     Workspace &wf = get_workspace(sp, t.ldf, base.prec, 1000);
-    DBuf<double> gloc, mloc, mu, om;
-    gloc.alloc((size_t)F.R * t.ldc);
-    mu.alloc((size_t)nsamp * F.N);
-    om.upload(t.omega, s);
+    PBuf<double> gloc, mloc, mu, om;
+    gloc.alloc(pool, (size_t)F.R * t.ldc);
+    mu.alloc(pool, (size_t)nsamp * F.N);
+    om.upload(pool, t.omega, s);
     global_to_local(F, gloc.p, gin.p, nsamp, t.ldc, s);
     const double *load = gloc.p;
     for (int pass = t.passes - 1; pass >= 0; --pass) {
@@ -2661,7 +2765,7 @@ static void run_grad(gf_tape &t, const double *g_in, double *grad, int mem, gf_s
         quadrature_sum(F, mu.p, wf.x.p, om.p, K, nsamp, t.ldf, s);
         global_to_local(F, gloc.p, mu.p, nsamp, t.ldc, s);
         if (pass > 0) {
-          mloc.alloc((size_t)F.R * t.ldc);
+          mloc.alloc_zero(pool, (size_t)F.R * t.ldc, s);  // (its ghost rows go into the batch)
           apply_level<double>(F, GF_APPLY_STENCIL, gloc.p, mloc.p, wf.one64.p, wf.zero64.p, t.ldc, t.ldc / CT,
                               nullptr, s);
           load = mloc.p;
@@ -2671,7 +2775,6 @@ static void run_grad(gf_tape &t, const double *g_in, double *grad, int mem, gf_s
         }
       }
     }
-    HIPCHK(hipStreamSynchronize(s));  // before gloc, mloc, mu and om are released
   } else {
     global_to_local(F, wc->r.p, gin.p, nsamp, t.ldc, s);
   }
@@ -2759,17 +2862,18 @@ static void run_eval(const gf_space *csp, int npts, const int32_t *patch, const 
   std::vector<int32_t> ph;
   std::vector<double> sh;
   check_points(sp, npts, patch, st, mem, ph, sh);
-  DBuf<int> pd;
-  DBuf<double> sd;
+  const std::shared_ptr<Pool> &pool = sp->ctx->pool;
+  PBuf<int> pd;
+  PBuf<double> sd;
   if (npts > 0) {
-    pd.upload(ph, s);
-    sd.upload(sh, s);
+    pd.upload(pool, ph, s);
+    sd.upload(pool, sh, s);
   }
   const size_t nin = (size_t)nvec * (adjoint ? npts : F.N), nout = (size_t)nvec * (adjoint ? F.N : npts);
   InArray a;
-  stage_in(a, in, nin, mem, s);
+  stage_in(sp->ctx, a, in, nin, mem, s);
   OutArray o;
-  stage_out(o, out, nout, mem);
+  stage_out(sp->ctx, o, out, nout, mem);
   if (adjoint) {
     // per global coefficient, the (point, basis function) entries that touch it, in ascending point
     // order: the gather then sums them in that order (no atomics, the same result on every run).  The
@@ -2790,13 +2894,13 @@ static void run_eval(const gf_space *csp, int npts, const int32_t *patch, const 
     for (int gi = 0; gi < F.N; ++gi) cnt[(size_t)gi + 1] += cnt[gi];
     std::vector<int> fill(cnt.begin(), cnt.end() - 1), ent(std::max<size_t>(1, gids.size()));
     for (size_t k = 0; k < gids.size(); ++k) ent[fill[gids[k]]++] = (int)k;
-    DBuf<int> dptr, dent;
-    DBuf<double> w;
-    dptr.upload(cnt, s);
-    dent.upload(ent, s);
-    w.alloc(std::max<size_t>(1, gids.size()));
+    PBuf<int> dptr, dent;
+    PBuf<double> w;
+    dptr.upload(pool, cnt, s);
+    dent.upload(pool, ent, s);
+    w.alloc(pool, std::max<size_t>(1, gids.size()));
     launch_eval_adjoint(F, npts, sd.p, dptr.p, dent.p, w.p, nvec, a.p, o.p, s);
-    finish_out(o, s);  // synchronises before the work arrays are released
+    finish_out(o, s);  // synchronises before the host lists are released
   } else {
     launch_eval(F, npts, pd.p, sd.p, nvec, a.p, o.p, s);
     finish_out(o, s);
@@ -2959,17 +3063,17 @@ gf_status gf_sqrt_mass(gf_space *sp, int32_t nsamp, const double *y, double *f, 
     const double setup_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - c0).count();
     const size_t nv = (size_t)nsamp * F.N;
     InArray yin;
-    stage_in(yin, y, nv, mem, s);
+    stage_in(sp->ctx, yin, y, nv, mem, s);
     OutArray fout;
-    stage_out(fout, f, nv, mem);
+    stage_out(sp->ctx, fout, f, nv, mem);
     hipEvent_t t0, t1;
     HIPCHK(hipEventCreate(&t0));
     HIPCHK(hipEventCreate(&t1));
     HIPCHK(hipEventRecord(t0, s));
     const int64_t sync0 = sp->ctx->host_syncs;
     const int ldc = round_up(nsamp, CT), ncols = khat * nsamp, ldf = round_up(ncols, CT);
-    DBuf<double> yl;
-    yl.alloc((size_t)F.R * ldc);
+    PBuf<double> yl;
+    yl.alloc(sp->ctx->pool, (size_t)F.R * ldc);
     global_to_local(F, yl.p, yin.p, nsamp, ldc, s);
     Workspace &w = get_workspace(sp, ldf, GF_PREC_FP64, 4000);
     replicate_cols(F, w.r.p, ldf, yl.p, ldc, nsamp, khat, s);
@@ -2980,9 +3084,9 @@ gf_status gf_sqrt_mass(gf_space *sp, int32_t nsamp, const double *y, double *f, 
     // g = c sum_k a_k z_k (ascending k), f = M g
     std::vector<double> om(khat);
     for (int k = 0; k < khat; ++k) om[k] = c * a[k];
-    DBuf<double> omd, g;
-    omd.upload(om, s);
-    g.alloc(nv);
+    PBuf<double> omd, g;
+    omd.upload(sp->ctx->pool, om, s);
+    g.alloc(sp->ctx->pool, nv);
     quadrature_sum(F, g.p, w.x.p, omd.p, khat, nsamp, ldf, s);
     global_to_local(F, yl.p, g.p, nsamp, ldc, s);
     apply_level<double>(F, GF_APPLY_STENCIL, yl.p, w.q.p, w.one64.p, w.zero64.p, ldc, ldc / CT, nullptr, s);
@@ -3067,7 +3171,7 @@ gf_status gf_solve_shifted(gf_space *sp, int32_t nsys, const double *sigma, cons
     if (opts->precision != GF_PREC_FP64 && opts->precision != GF_PREC_MIXED) fail(GF_EINVAL, "unknown precision");
     if (!(opts->rtol > 0.0) || !(opts->rtol < 1.0)) fail(GF_EINVAL, "rtol must be in (0, 1)");
     if (opts->max_iter < 1) fail(GF_EINVAL, "max_iter must be >= 1");
-    if (opts->cheb_degree < 0 || opts->cheb_degree > 16) fail(GF_EINVAL, "cheb_degree must be in 0..16");
+    if (opts->cheb_degree < 0 || opts->cheb_degree > kMaxCheb) fail(GF_EINVAL, "cheb_degree must be in 0..16");
     if (opts->apply_kind != GF_APPLY_STENCIL && opts->apply_kind != GF_APPLY_SUMFACT)
       fail(GF_EINVAL, "unknown apply_kind");
     if (opts->preconditioner != GF_PRECOND_VCYCLE && opts->preconditioner != GF_PRECOND_BPX)
@@ -3102,9 +3206,9 @@ gf_status gf_solve_shifted(gf_space *sp, int32_t nsys, const double *sigma, cons
     }
     const size_t nv = (size_t)nsys * F.N;
     InArray bin;
-    stage_in(bin, b, nv, mem, s);
+    stage_in(sp->ctx, bin, b, nv, mem, s);
     OutArray xout;
-    stage_out(xout, x, nv, mem);
+    stage_out(sp->ctx, xout, x, nv, mem);
     const int ldb = round_up(nsys, CT);
     const int prec = mass ? GF_PREC_FP64 : opts->precision;
     Workspace &w = get_workspace(sp, ldb, prec, 3000);
