@@ -369,9 +369,10 @@ struct SmoothLog {
 struct Workspace {
   SmoothLog *slog = nullptr;  // set while a timed batch runs
   int ldb = 0, ntiles = 0, prec = 0;
-  // structure of the columns' shifts in the current batch: the most distinct shifts in one column tile,
-  // and whether every aligned group of 16 columns has one shift (see EpiArgs::nslot, rows16)
-  int nslot = 0, rows16 = 0;
+  // whether every aligned group of 16 columns of the current batch has one shift (see EpiArgs::rows16):
+  // with the padding columns counted as part of the group they complete (rows16), and with the padding
+  // at a shift of its own, 1 (full16)
+  int rows16 = 0, full16 = 0;
   DBuf<double> x, r, p, q;  // outer CG (FP64)
   // mixed precision: the search direction stored in FP32 (see BatchSolve::p32)
   DBuf<float> p32;
@@ -563,12 +564,10 @@ struct Prec<float> {
 // takes the separate-stencil kernel (same launch shapes).
 static bool g_autotune = true;
 
-static int stencil_mode_class(int nslot, int rows16) { return rows16 ? 2 : (nslot >= 1 && nslot <= 8 ? 0 : 1); }
-
 template <typename T>
 static const ApplyTune &get_tune(const Level &L, int ldb, int ntiles, const T *x, const T *ca, const T *cb,
                                  const EpiArgs<T> &ecall, hipStream_t s) {
-  const auto key = std::make_tuple((int)sizeof(T), ldb, ecall.kind, stencil_mode_class(ecall.nslot, ecall.rows16));
+  const auto key = std::make_tuple((int)sizeof(T), ldb, ecall.kind, ecall.rows16 ? 2 : 1);
   auto it = L.tune.find(key);
   if (it != L.tune.end()) return it->second;
   ApplyTune best;
@@ -586,7 +585,7 @@ static const ApplyTune &get_tune(const Level &L, int ldb, int ntiles, const T *x
   if (g_autotune && L.n1 >= 8) {
     std::vector<ApplyTune> cand;
     for (int ty : {1, 2, 4}) {
-      if (ty == 4 && L.p > 3) continue;
+      if (ty == 4 && (L.p > 3 || (L.p == 3 && !ecall.rows16))) continue;
       if (ty > 1 && L.p >= 4) continue;
       for (int tx : {32, 64}) {
         if (tx > 2 * L.n1 && tx != 32) continue;
@@ -632,7 +631,7 @@ static const ApplyTune &get_tune(const Level &L, int ldb, int ntiles, const T *x
       const float us = ms * 1e3f / 3.f;
       if (std::getenv("GF_TUNE_LOG"))
         std::fprintf(stderr, "tune p=%d lev=%d T=%d ldb=%d kind=%d mode=%d algo=%d TY=%d TX=%d: %.1f us\n", L.p, L.lev,
-                     (int)sizeof(T), ldb, e.kind, stencil_mode_class(e.nslot, e.rows16), t.algo, t.TY, t.TX, us);
+                     (int)sizeof(T), ldb, e.kind, e.rows16 ? 2 : 1, t.algo, t.TY, t.TX, us);
       if (us < best_us) {
         best_us = us;
         best = t;
@@ -750,7 +749,6 @@ static void apply_level(const Level &L, int kind, const T *x, T *y, const T *ca,
   EpiArgs<T> e;
   e.kind = EPI_STORE;
   e.y = y;
-  e.nslot = uniform ? 1 : 0;
   e.rows16 = uniform ? 1 : 0;
   Scratch none;
   apply_epi<T>(L, kind, x, ca, cb, e, none, nullptr, const_cast<int *>(active), ldb, ntiles, 0.0, 0, s);
@@ -1073,7 +1071,6 @@ static T *vcycle(gf_space *sp, Workspace &w, const SolveSpec &spec, int li, cons
   auto smooth = [&](int k, bool last, int dflags) {
     EpiArgs<T> e;
     e.kind = EPI_CHEB;
-    e.nslot = w.nslot;
     e.rows16 = w.rows16;
     e.dflags = dflags | (k > 0 ? 4 : 0);
     e.y = a;
@@ -1122,7 +1119,6 @@ static T *vcycle(gf_space *sp, Workspace &w, const SolveSpec &spec, int li, cons
   {
     EpiArgs<T> e;
     e.kind = EPI_RESID;
-    e.nslot = w.nslot;
     e.rows16 = w.rows16;
     e.y = a;
     e.r = r;
@@ -1224,24 +1220,19 @@ struct BatchSolve {
     for (int c = 0; c < ldb; ++c) {
       cs[c] = ColState{};
       cs[c].done = (c < spec.ncols) ? 0 : 1;
-      sig[c] = c < spec.ncols ? spec.col_sig[c] : 1.0;
-      node[c] = c < spec.ncols ? spec.col_node[c] : 0;
+      // (padding columns take the last system's shift, so that the group of 16 they complete has one)
+      sig[c] = spec.col_sig[std::min(c, spec.ncols - 1)];
+      node[c] = spec.col_node[std::min(c, spec.ncols - 1)];
       sigf[c] = (float)sig[c];
     }
     std::fill(w->active_h.begin(), w->active_h.end(), 0);
     for (int c = 0; c < spec.ncols; ++c) w->active_h[c / CT] = 1;
     std::copy(w->active_h.begin(), w->active_h.end(), act);
-    // shift structure of the column tiles (padding columns carry the shift 1)
-    w->nslot = 0;
-    w->rows16 = 1;
-    for (int t = 0; t < w->ntiles; ++t) {
-      std::vector<double> d;
-      for (int c = t * CT; c < (t + 1) * CT; ++c) {
-        if ((c == t * CT || sig[c] != sig[c - 1]) && std::find(d.begin(), d.end(), sig[c]) == d.end())
-          d.push_back(sig[c]);
-        if (c % 16 != 0 && sig[c] != sig[c - 1]) w->rows16 = 0;
-      }
-      w->nslot = std::max(w->nslot, (int)d.size());
+    w->rows16 = w->full16 = 1;
+    for (int c = 0; c < ldb; ++c) {
+      if (c % 16 == 0) continue;
+      if (sig[c] != sig[c - 1]) w->rows16 = w->full16 = 0;
+      if (c == spec.ncols && sig[c] != 1.0) w->full16 = 0;
     }
     // Chebyshev coefficients of every smoothing step per system (the interval depends on the node)
     size_t used = w->cf_off;
@@ -1320,7 +1311,7 @@ struct BatchSolve {
   void start(hipStream_t s) {
     const Level &F = sp->fine();
     p32 = mixed() && !spec.mass_shift && spec.kind == GF_APPLY_STENCIL && spec.precond == GF_PRECOND_VCYCLE &&
-          sp->nlev() > 1 && w->rows16 && w->p32.p && outer_p32_fits(F, w->ldb);
+          sp->nlev() > 1 && w->full16 && w->p32.p && outer_p32_fits(F, w->ldb);
     // the smoothing launches of the first preconditioner application are timed with the others
     w->slog = (spec.flags & GF_FLAG_TIME_APPLY) ? &slog : nullptr;
     slog.first_phase = true;
@@ -1358,7 +1349,6 @@ struct BatchSolve {
     Scratch sc = w->scratch();
     EpiArgs<double> e;
     e.kind = EPI_STORE;
-    e.nslot = w->nslot;
     e.rows16 = w->rows16;
     e.y = w->q.p;
     e.dot = 1;
@@ -1519,8 +1509,7 @@ static std::string graph_key(const std::vector<BatchSolve *> &items, int chunk) 
     const SolveSpec &sp = it->spec;
     os << "|" << (const void *)it->sp << "," << (const void *)&w << "," << w.ldb
        << "," << sp.prec << "," << sp.kind << "," << sp.cheb << "," << sp.rtol << "," << sp.max_iter << ","
-       << sp.flags << "," << w.ncols << "," << sp.precond << "," << sp.mass_shift << "," << sp.smooth_load << "," << w.nslot << ","
-       << w.rows16 << "," << it->p32 << "," << (const void *)w.x.p << "," << (const void *)w.r.p << ","
+       << sp.flags << "," << w.ncols << "," << sp.precond << "," << sp.mass_shift << "," << sp.smooth_load << "," << w.rows16 << "," << it->p32 << "," << (const void *)w.x.p << "," << (const void *)w.r.p << ","
        << (const void *)w.p.p << "," << (const void *)w.p32.p << "," << (const void *)w.q.p << "," << (const void *)w.cs.p << "," << (const void *)w.partial.p << ","
        << (const void *)w.active.p << "," << (const void *)w.sig64.p;
     os << "," << (const void *)w.Ainv.p;
@@ -2215,7 +2204,6 @@ gf_status gf_space_apply_noalloc(const gf_space *csp, double sigma, double s_sca
       EpiArgs<double> e;
       e.kind = EPI_STORE;
       e.y = Y;
-      e.nslot = 1;
       e.rows16 = 1;
       Scratch none;
       apply_fused<double>(F, F.stM.p, F.stS.p, X, ca, cb, e, none, nullptr, nullptr, ldb, nt, 0.0, 0, s, t);

@@ -292,15 +292,18 @@ void finalize(int nslot, int nd, int op, Scratch &sc, ColState *cs, int *active,
 // ------------------------------------------------------------------ launchers
 static int xcd_q(int total) { return (total + 7) / 8; }
 
+// strips of the separate stencils (SM_PAIR): four rows of degree 3 hold too much to be unrolled
+template <int P, int TY>
+constexpr bool kPairRows = !(P == 3 && TY == 4);
+
 template <typename T, int P, int TY, int KIND, int DOT>
 static void launch_apply_k(const ApplyGeom &g, int algo, const T *stM, const T *stS, const T *x, const T *ca,
                            const T *cb, const EpiArgs<T> &e, double *partial, const int *active, hipStream_t s,
                            hipEvent_t ev0, hipEvent_t ev1) {
   // with events the runtime stamps them at the start and end of this dispatch itself
   if (algo == 1) {
-    auto kern = e.rows16 ? k_stencil<T, P, TY, KIND, DOT, SM_DPP>
-                : (e.nslot >= 1 && e.nslot <= StencilSlots<T, P, TY>::value) ? k_stencil<T, P, TY, KIND, DOT, SM_COMB>
-                                                                            : k_stencil<T, P, TY, KIND, DOT, SM_PAIR>;
+    constexpr int PAIR = kPairRows<P, TY> ? SM_PAIR : SM_DPP;  // (the latter is not reached, see apply_fused)
+    auto kern = e.rows16 ? k_stencil<T, P, TY, KIND, DOT, SM_DPP> : k_stencil<T, P, TY, KIND, DOT, PAIR>;
     if (ev0)
       hipExtLaunchKernelGGL(kern, dim3(8 * g.q), dim3(256), 0, s, ev0, ev1, 0, g, stM, stS, x, ca, cb, e.cf1, e.cf2,
                             e.y, e.zout, e.r, partial, active, e.dflags, e.q2);
@@ -409,8 +412,10 @@ void apply_fused(const Level &L, const T *stM, const T *stS, const T *x, const T
                  const EpiArgs<T> &e, Scratch &sc, ColState *cs, int *active, int ldb, int ntiles, double tol2,
                  int maxit, hipStream_t s, const ApplyTune &tune, hipEvent_t ev0, hipEvent_t ev1) {
   ApplyGeom g = apply_geom(L, ldb, ntiles, tune.TY, tune.TX, tune.NC);
-  g.grp = std::max(1, std::min(tune.grp, g.nsb));
   int algo = tune.algo;
+  if (algo == 1 && L.p == 3 && g.TY == 4 && !e.rows16)
+    g = apply_geom(L, ldb, ntiles, 2, tune.TX, tune.NC);
+  g.grp = std::max(1, std::min(tune.grp, g.nsb));
   if (algo == 1 && !stencil_offsets_fit(L, ldb, g.TY, (int)sizeof(T))) {
     // the combined-stencil kernel addresses vectors by 32-bit offsets from the strip's first row
     algo = 0;

@@ -46,46 +46,30 @@ __device__ __forceinline__ void block_partial2(double acc0, double acc1, double 
 
 // ------------------------------------------------------------------ combined-stencil kernel
 // The same operator and epilogues as k_apply_fused, organised around two observations.
-//  * Every system of a column tile applies ca M + cb S with its own (ca, cb); the tiles of the solver
-//    hold few distinct pairs (the samples of one sinc node share the shift).  Each wavefront finds the
-//    distinct pairs of its tile once (ballot over the lanes), and per output row stages one combined
-//    stencil ca_d M_i + cb_d S_i per distinct pair d in its LDS slot; a lane then needs one LDS read and
-//    one multiply-add per tap instead of one read and two multiply-adds.  A tile with more distinct
-//    pairs than the slots hold falls back to the separate (M_i, S_i) pairs of k_apply_fused.  The
-//    Jacobi diagonal of an interior row is the centre of its combined stencil (interior unknowns have
-//    one copy), so the smoothing step reads no diagonal vectors.
+//  * Every system of a column tile applies ca M + cb S with its own (ca, cb), but the taps M_i and S_i
+//    are the row's: lanes hold them once per row and broadcast them to the multiply-adds, from
+//    registers (see StencilMode).  The Jacobi diagonal of an interior row is the centre of its stencil
+//    (interior unknowns have one copy), so the smoothing step reads no diagonal vectors.
 //  * Vector memory loads return in order, so a load issued after another cannot complete first.  All
 //    loads of a step -- the window's next column, the stencils of the next step's rows and the
 //    epilogue's right-hand side and previous iterate -- are issued one step ahead, before the arithmetic
 //    of the current step; the waits of a step then cover only loads issued a full step earlier.
 //    For degrees up to 3 the step loop is unrolled by the stencil width, so the window rotates by
 //    register renaming instead of register moves.
-template <typename T>
-__device__ __forceinline__ T read_lane(T v, int l);
-template <>
-__device__ __forceinline__ float read_lane<float>(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-template <>
-__device__ __forceinline__ double read_lane<double>(double v, int l) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), l);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-__device__ __forceinline__ unsigned long long bit_pattern(float v) { return __float_as_uint(v); }
-__device__ __forceinline__ unsigned long long bit_pattern(double v) {
-  return (unsigned long long)__double_as_longlong(v);
-}
 
-// How a strip applies ca M + cb S (chosen by the host from what it knows of the column tiles):
-//   SM_COMB  one combined stencil per distinct (ca, cb) of the tile in LDS, one broadcast read per tap
-//   SM_PAIR  the separate M and S stencils in LDS, two reads and two multiply-adds per tap (any tile)
-//   SM_DPP   (ca, cb) is the same within each aligned group of 16 columns: every lane combines 16 taps
-//            of the stencils with its own (ca, cb) into one register, and each tap is one multiply-add
-//            whose coefficient operand is broadcast within the 16 lanes by the DPP row_newbcast
-//            modifier -- no LDS read per tap
-enum StencilMode { SM_COMB = 0, SM_PAIR = 1, SM_DPP = 2 };
+// How a strip applies ca M + cb S (chosen by the host from what it knows of the column tiles); the lanes
+// of every aligned 16-lane row hold 16 taps of a stencil per register, and each tap is a multiply-add whose
+// coefficient operand is broadcast within the 16 lanes by the DPP row_newbcast modifier -- no LDS read
+// per tap:
+//   SM_DPP   (ca, cb) is the same within each aligned group of 16 columns: the registers hold the
+//            combined stencil, one multiply-add per tap
+//   SM_PAIR  any columns: the stencils of M and S apart, two multiply-adds per tap
+// Measured against the LDS forms that SM_PAIR replaced (a broadcast LDS read for every multiply-add of
+// a tap, or one combined stencil in LDS for each of up to eight shifts of a tile): 41 nodes on degree 3,
+// 128 x 128, FP32 V-cycle, 5 samples a node (11 to 13 shifts a tile) 45.8 -> 43.9 ms, 20 samples (4 shifts)
+// 100.9 -> 96.6 ms; degree 2, 64 x 64, FP64, 20 samples 22.3 -> 20.7 ms; six requests on 32 x 32 23.0 ->
+// 20.8 ms.  The LDS pipe serves one wavefront of a compute unit at a time, the vector ALUs all four.
+enum StencilMode { SM_PAIR = 1, SM_DPP = 2 };
 
 // acc += (lane J of this lane's 16-lane row of c) * x.  The compiler does not fold its own DPP moves
 // into multiply-adds, so the instruction is written out; the first tap of a chunk waits the two
@@ -119,11 +103,10 @@ __device__ __forceinline__ double row_bcast(double v) {
   return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + J, 0xf, 0xf, true);
 }
 
-// In DPP mode the taps are summed column by column: the o-th multiply-add of a row's chain takes tap
+// The taps are summed column by column: the o-th multiply-add of a row's chain takes tap
 // (dy, dx) = (o mod S, o / S), tap index dy S + dx.  The window's leftmost column (dx = 0) is then dead
 // after the first S multiply-adds of every row, and the next column is loaded into its registers while
-// the other columns are summed (no staging registers for it).  The LDS modes sum row by row (tap
-// order), which lets the compiler read the coefficients of consecutive taps in wide LDS reads.
+// the other columns are summed (no staging registers for it).
 template <int S>
 constexpr int tap_at(int o) {
   return (o % S) * S + o / S;
@@ -136,7 +119,7 @@ constexpr bool chunk_first(int o) {
   return true;
 }
 
-// acc[t] += the multiply-adds o in [O, O1) of the NT rows of a step, in DPP mode: tap (dy, dx) takes its
+// acc[t] += the multiply-adds o in [O, O1) of the NT rows of a step: tap (dy, dx) takes its
 // coefficient from chunk tap / 16, lane tap % 16, and the window column (u + dx) mod U of row t + dy;
 // the rows' chains are interleaved (independent multiply-adds back to back)
 template <typename T, int S, int U, int NT, int O, int O1, typename Win>
@@ -148,18 +131,6 @@ __device__ __forceinline__ void dpp_taps(T (&acc)[NT], const T (&c)[NT][(S * S +
       fma_row_bcast<tap % 16, chunk_first<S>(O)>(acc[t], c[t][tap / 16], win[t + dy][(U == S) ? (u + dx) % S : dx]);
     dpp_taps<T, S, U, NT, O + 1, O1>(acc, c, win, u);
   }
-}
-
-// the stencil sum of row t with coefficients from a stencil in LDS (lc[tap]), in tap order
-template <typename T, int S, int U, typename Win>
-__device__ __forceinline__ T lds_taps(const T *lc, const Win &win, int t, int u) {
-  T acc = 0;
-#pragma unroll
-  for (int o = 0; o < S * S; ++o) {
-    const int dy = o / S, dx = o % S;
-    acc = fma(lc[o], win[t + dy][(U == S) ? (u + dx) % S : dx], acc);
-  }
-  return acc;
 }
 
 // Raw buffer accesses: a wavefront-uniform 128-bit descriptor (base address in scalar registers) plus a
@@ -184,13 +155,6 @@ __device__ __forceinline__ void buf_st(double v, __amdgpu_buffer_rsrc_t r, uint3
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(buf_v2u, v), r, vo, so, 0);
 }
 
-// slots of combined stencils per wavefront: as many as keep the block's LDS at 32 KiB
-template <typename T, int P, int TY>
-struct StencilSlots {
-  static constexpr int SS = (2 * P + 1) * (2 * P + 1);
-  static constexpr int value = (4 * TY * 8 * SS * (int)sizeof(T) <= 32768) ? 8 : 4;
-};
-
 // One strip of TY rows x [x0, x1) of one patch for one column tile (lane = system), in stencil mode
 // MODE.  Returns the lane's share of the epilogue's inner product.
 template <typename T, int P, int TY, int KIND, int DOT, int MODE, typename XT>
@@ -198,12 +162,10 @@ __device__ __forceinline__ double stencil_strip(const ApplyGeom &g, const T *__r
                                                 const T *__restrict__ stS, const XT *__restrict__ x,
                                                 T *__restrict__ y, T *__restrict__ zout, const T *__restrict__ r,
                                                 int m, int iy0, int x0, int x1, int64_t ct0, int lane, T *lds,
-                                                const T *sab, int slot, int nd, T a, T b, T a1, T a2, int dflags,
+                                                T a, T b, T a1, T a2, int dflags,
                                                 const double *__restrict__ q2, double &acc2) {
   constexpr int S = 2 * P + 1, SS = S * S, WR = TY + 2 * P, NH = (SS + 63) / 64, NCH = (SS + 15) / 16;
-  constexpr bool PAIR = MODE != SM_COMB;
   constexpr int U = (P <= 3) ? S : 1;
-  constexpr int MAXD = StencilSlots<T, P, TY>::value;
   const int W = g.W, n1 = g.n1;
   const int64_t ldb = g.ldb;
   const int64_t pbase = (int64_t)m * W * W;
@@ -243,7 +205,7 @@ __device__ __forceinline__ double stencil_strip(const ApplyGeom &g, const T *__r
   // slot of column dx = 0 once that column's multiply-adds are issued.  Shifting window (U = 1): columns
   // x0 .. x0 + 2P - 1 in slots 1 .. S-1, column x0 + 2P in nxt; each step shifts the slots down by one,
   // appends nxt and loads the next column into nxt before its arithmetic.
-  T win[WR][S], nxt[WR];
+  T win[WR][S], nxt[U == S ? 1 : WR];
 #pragma unroll
   for (int k = 0; k < WR; ++k) {
     if constexpr (U == S) {
@@ -295,17 +257,13 @@ __device__ __forceinline__ double stencil_strip(const ApplyGeom &g, const T *__r
       // S_i), then reuse their registers for the next step's loads
 #pragma unroll
       for (int t = 0; t < TY; ++t) {
-        T *lt = lds + t * MAXD * SS;
+        T *lt = lds + t * 2 * SS;
 #pragma unroll
         for (int h = 0; h < NH; ++h) {
           const int l = h * 64 + lane;
           if (l < SS) {
-            if (PAIR) {
-              lt[l] = cmn[t][h];
-              lt[SS + l] = csn[t][h];
-            } else {
-              for (int d = 0; d < nd; ++d) lt[d * SS + l] = sab[2 * d] * cmn[t][h] + sab[2 * d + 1] * csn[t][h];
-            }
+            lt[l] = cmn[t][h];
+            lt[SS + l] = csn[t][h];
           }
         }
       }
@@ -325,55 +283,42 @@ __device__ __forceinline__ double stencil_strip(const ApplyGeom &g, const T *__r
           qv[t] = buf_ld(double(), bq, (uint32_t)lane * 8u, (ooff[t] + (uint32_t)ix) * (uint32_t)ldb * 8u);
       }
       __builtin_amdgcn_wave_barrier();
-      // DPP mode: chunk k of row t holds taps 16k .. 16k+15 of this lane's combined stencil in the
-      // lanes of every 16-lane row
-      T cc[TY][NCH];
-      if (MODE == SM_DPP) {
+      // chunk k of row t holds taps 16k .. 16k+15 in the lanes of every 16-lane row, of this
+      // lane's combined stencil (SM_DPP) or of M (cc) and S (c2) apart
+      T cc[TY][NCH], c2[TY][NCH];
 #pragma unroll
-        for (int t = 0; t < TY; ++t)
+      for (int t = 0; t < TY; ++t)
 #pragma unroll
-          for (int k = 0; k < NCH; ++k) {
-            const int tap = min(16 * k + (lane & 15), SS - 1);
-            cc[t][k] = (16 * k + (lane & 15) < SS) ? a * lds[t * MAXD * SS + tap] + b * lds[t * MAXD * SS + SS + tap]
-                                                   : T(0);
-          }
-      }
-      // DPP mode: the stencil sums of all TY rows before the epilogue, column dx = 0 first, then the
-      // next step's newest column into that column's slot.  LDS modes: the next column into nxt now,
-      // each row's sum in the epilogue (one row's coefficient reads in flight), nxt into the freed
-      // slot after it.
-      T ac[TY];
-      if constexpr (MODE == SM_DPP) {
-#pragma unroll
-        for (int t = 0; t < TY; ++t) ac[t] = 0;
-        if constexpr (U == S) {
-          dpp_taps<T, S, U, TY, 0, S>(ac, cc, win, u);
-#pragma unroll
-          for (int k = 0; k < WR; ++k) win[k][u % S] = ldx(woff[k] + (uint32_t)(ixn + 2 * P) * colbx);
-          dpp_taps<T, S, U, TY, S, S * S>(ac, cc, win, u);
-        } else {
-          dpp_taps<T, S, U, TY, 0, S * S>(ac, cc, win, u);
+        for (int k = 0; k < NCH; ++k) {
+          // (lanes past the last tap hold its value, which no tap reads from them)
+          const int tap = min(16 * k + (lane & 15), SS - 1);
+          const T cm = lds[t * 2 * SS + tap], cs = lds[t * 2 * SS + SS + tap];
+          cc[t][k] = MODE == SM_DPP ? a * cm + b * cs : cm;
+          c2[t][k] = cs;
         }
-      } else if constexpr (U == S) {
+      // the stencil sums of all TY rows before the epilogue, column dx = 0 first, then the next step's
+      // newest column into that column's slot
+      constexpr int O1 = U == S ? S : S * S;
+      T ac[TY], as[TY];
 #pragma unroll
-        for (int k = 0; k < WR; ++k) nxt[k] = ldx(woff[k] + (uint32_t)(ixn + 2 * P) * colbx);
+      for (int t = 0; t < TY; ++t) ac[t] = as[t] = 0;
+      dpp_taps<T, S, U, TY, 0, O1>(ac, cc, win, u);
+      if constexpr (MODE == SM_PAIR) dpp_taps<T, S, U, TY, 0, O1>(as, c2, win, u);
+      if constexpr (U == S) {
+#pragma unroll
+        for (int k = 0; k < WR; ++k) win[k][u % S] = ldx(woff[k] + (uint32_t)(ixn + 2 * P) * colbx);
+        dpp_taps<T, S, U, TY, S, S * S>(ac, cc, win, u);
+        if constexpr (MODE == SM_PAIR) dpp_taps<T, S, U, TY, S, S * S>(as, c2, win, u);
       }
 #pragma unroll
       for (int t = 0; t < TY; ++t) {
         const int iy = iy0 + t;
         if (iy >= n1) break;
-        const T *lt = lds + t * MAXD * SS;
-        T Az, D;
-        if (MODE == SM_DPP) {
-          Az = ac[t];
-          D = row_bcast<(P * S + P) % 16>(cc[t][(P * S + P) / 16]);
-        } else if (PAIR) {  // slot 0 holds M_i, slot 1 S_i
-          const T am = lds_taps<T, S, U>(lt, win, t, u);
-          Az = a * am + b * lds_taps<T, S, U>(lt + SS, win, t, u);
-          D = a * lt[P * S + P] + b * lt[SS + P * S + P];
-        } else {
-          Az = lds_taps<T, S, U>(lt + slot * SS, win, t, u);
-          D = lt[slot * SS + P * S + P];
+        constexpr int CT0 = (P * S + P) / 16, CL = (P * S + P) % 16;  // the centre tap
+        T Az = ac[t], D = row_bcast<CL>(cc[t][CT0]);
+        if (MODE == SM_PAIR) {
+          Az = a * ac[t] + b * as[t];
+          D = a * D + b * row_bcast<CL>(c2[t][CT0]);
         }
         const uint32_t so = (ooff[t] + (uint32_t)ix) * colb;
         const T zc = win[t + P][(U == S) ? (u + P) % S : P];
@@ -401,10 +346,6 @@ __device__ __forceinline__ double stencil_strip(const ApplyGeom &g, const T *__r
           if constexpr (DOT == 2) acc2 += (double)zo * qv[t];
         }
       }
-      if constexpr (MODE != SM_DPP && U == S) {
-#pragma unroll
-        for (int k = 0; k < WR; ++k) win[k][u % S] = nxt[k];
-      }
       // the next step's staging overwrites this step's stencils only after these reads (LDS
       // instructions of one wavefront execute in order)
       __builtin_amdgcn_wave_barrier();
@@ -429,9 +370,7 @@ void k_stencil(ApplyGeom g, const T *__restrict__ stM, const T *__restrict__ stS
                                                  const int *__restrict__ active, int dflags,
                                                  const double *__restrict__ q2) {
   constexpr int SS = (2 * P + 1) * (2 * P + 1);
-  constexpr int MAXD = StencilSlots<T, P, TY>::value;
-  __shared__ __attribute__((aligned(16))) T lds_all[4][TY * MAXD * SS];
-  __shared__ T sab_all[4][2 * MAXD];
+  __shared__ __attribute__((aligned(16))) T lds_all[4][TY * 2 * SS];
   const int Lb = blockIdx.x;
   const int bl = (Lb & 7) * g.q + (Lb >> 3);
   if (bl >= g.nsb * g.ntiles) return;
@@ -463,31 +402,8 @@ void k_stencil(ApplyGeom g, const T *__restrict__ stM, const T *__restrict__ stS
       if (dflags & 4) a1 = cf1[col];
       a2 = cf2[col];
     }
-    T *sab = sab_all[wave];
-    int slot = 0, nd = 0;
-    if (MODE == SM_COMB) {
-      // distinct (a, b) pairs of the tile by bit pattern (every lane matches itself, so the loop ends
-      // after at most 64 rounds); the caller guarantees at most MAXD of them
-      unsigned long long rem = ~0ull;
-      const unsigned long long ka = bit_pattern(a), kb = bit_pattern(b);
-      while (rem) {
-        const int l = __builtin_ctzll(rem);
-        const T al = read_lane(a, l), bl2 = read_lane(b, l);
-        const unsigned long long hit = __ballot(ka == bit_pattern(al) && kb == bit_pattern(bl2));
-        if (nd < MAXD) {
-          if ((hit >> lane) & 1ull) slot = nd;
-          if (lane == 0) {
-            sab[2 * nd] = al;
-            sab[2 * nd + 1] = bl2;
-          }
-          ++nd;
-        }
-        rem &= ~hit;
-      }
-      __builtin_amdgcn_wave_barrier();
-    }
     acc = stencil_strip<T, P, TY, KIND, DOT, MODE, XT>(g, stM, stS, x, y, zout, r, m, iy0, x0, x1, (int64_t)ct * CT,
-                                                   lane, lds_all[wave], sab, slot, nd, a, b, a1, a2, dflags, q2,
+                                                   lane, lds_all[wave], a, b, a1, a2, dflags, q2,
                                                    acc2);
   }
   if constexpr (DOT == 2)

@@ -177,16 +177,6 @@ static void run(int p, int lev, int nnode, int nsamp, const std::vector<std::str
     c1[c] = (T)U(rng);
     c2[c] = (T)U(rng);
   }
-  int nslot = 0;
-  for (int t = 0; t < nt; ++t) {
-    std::vector<T> d;
-    for (int c = t * 64; c < t * 64 + 64; ++c) {
-      bool f = false;
-      for (T v : d) f = f || v == ca[c];
-      if (!f) d.push_back(ca[c]);
-    }
-    nslot = std::max(nslot, (int)d.size());
-  }
   T *dca = dalloc<T>(ldb), *dcb = dalloc<T>(ldb), *dc1 = dalloc<T>(ldb), *dc2 = dalloc<T>(ldb);
   CK(hipMemcpy(dca, ca.data(), ldb * sizeof(T), hipMemcpyHostToDevice));
   CK(hipMemcpy(dcb, cb.data(), ldb * sizeof(T), hipMemcpyHostToDevice));
@@ -194,11 +184,10 @@ static void run(int p, int lev, int nnode, int nsamp, const std::vector<std::str
   CK(hipMemcpy(dc2, c2.data(), ldb * sizeof(T), hipMemcpyHostToDevice));
   const int nslots_part = partial_slots(L, ldb, nt) + 8;
   double *partial = dalloc<double>((size_t)nslots_part * ldb);
-  int *counter = dalloc<int>(nt);
   ColState *cs = dalloc<ColState>(ldb);
   CK(hipMemset(cs, 0, ldb * sizeof(ColState)));
   unsigned long long *cmp = dalloc<unsigned long long>(2);
-  Scratch sc{partial, counter};
+  Scratch sc{partial};
   hipEvent_t e0, e1;
   CK(hipEventCreate(&e0));
   CK(hipEventCreate(&e1));
@@ -277,7 +266,7 @@ static void run(int p, int lev, int nnode, int nsamp, const std::vector<std::str
     const double bytes = (double)vecs * sizeof(T) * ncols * rows + 2.0 * SS * sizeof(T) * rows;
     bool have_ref = false;
     for (int algo : algos)
-      for (int slotmode = 0; slotmode < (algo == 1 ? 3 : 1); ++slotmode)
+      for (int slotmode = 0; slotmode < (algo == 1 ? 2 : 1); ++slotmode)
         for (auto sh : shapes) {
           if (sh.TY == 4 && (sizeof(T) == 8 || p > 3)) continue;
           if (sh.TY == 4 && algo == 0) continue;
@@ -286,9 +275,8 @@ static void run(int p, int lev, int nnode, int nsamp, const std::vector<std::str
           tu.TX = sh.TX;
           tu.grp = sh.G;
           tu.algo = algo;
-          e.nslot = slotmode == 0 ? nslot : 0;  // 0: pair fallback
-          e.rows16 = slotmode == 2 ? 1 : 0;
-          if (slotmode == 2 && nsamp % 16 != 0) continue;
+          e.rows16 = slotmode;
+          if (slotmode == 1 && nsamp % 16 != 0) continue;
           // timing: one warm-up and five timed launches (z_prev restored before each)
           float tot = 0.f;
           for (int k = 0; k < 6; ++k) {
@@ -322,15 +310,14 @@ static void run(int p, int lev, int nnode, int nsamp, const std::vector<std::str
               (w ? errz : erry) = m > 0 ? d / m : d;
             }
           }
-          std::printf("%-8s algo=%d %s TY=%d TX=%-3d G=%-2d %9.1f us %7.1f GB/s (%.1f%%)  rel.err y %.2e z %.2e  nslot=%d\n",
-                      kind.c_str(), algo, slotmode == 2 ? "dpp " : slotmode ? "pair" : "comb", sh.TY, sh.TX, sh.G, us, bytes / (us * 1e-6) / 1e9,
-                      100.0 * bytes / (us * 1e-6) / 8e12, erry, errz, e.nslot);
+          std::printf("%-8s algo=%d %s TY=%d TX=%-3d G=%-2d %9.1f us %7.1f GB/s (%.1f%%)  rel.err y %.2e z %.2e\n",
+                      kind.c_str(), algo, slotmode ? "dpp " : "pair", sh.TY, sh.TX, sh.G, us, bytes / (us * 1e-6) / 1e9,
+                      100.0 * bytes / (us * 1e-6) / 8e12, erry, errz);
           std::fflush(stdout);
         }
   }
   for (T *q : {stM, stS, ddM, ddS, x, r, zo, zs, y, ry, rz, dca, dcb, dc1, dc2}) CK(hipFree(q));
   CK(hipFree(partial));
-  CK(hipFree(counter));
   CK(hipFree(cs));
   CK(hipFree(cmp));
 }
