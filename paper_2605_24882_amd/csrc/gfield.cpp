@@ -2818,24 +2818,26 @@ static void run_grad(gf_tape &t, const double *g_in, double *grad, int mem, gf_s
   if (tot.flags & 1) fail(GF_ENOCONV, "some adjoint system did not reach rtol within max_iter");
 }
 
-// host copies of evaluation points, validated
-static void check_points(const gf_space *sp, int npts, const int32_t *patch, const double *st, int mem,
-                         std::vector<int32_t> &ph, std::vector<double> &sh) {
-  ph.resize(npts);
-  sh.resize((size_t)2 * npts);
+// points of the evaluation, validated before any work
+static void check_points(gf_space *sp, int npts, const int32_t *patch, const double *st, int mem) {
+  int bad = 0;
   if (npts == 0) return;
   if (mem == GF_DEVICE) {
-    HIPCHK(hipMemcpy(ph.data(), patch, npts * sizeof(int32_t), hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(sh.data(), st, 2 * (size_t)npts * sizeof(double), hipMemcpyDeviceToHost));
+    hipStream_t s = sp->ctx->stream;
+    PBuf<int> flag;
+    flag.alloc(sp->ctx->pool, 1);
+    launch_check_points(sp->fine(), npts, patch, st, flag.p, s);
+    HIPCHK(hipMemcpyAsync(&bad, flag.p, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
   } else {
-    std::memcpy(ph.data(), patch, npts * sizeof(int32_t));
-    std::memcpy(sh.data(), st, 2 * (size_t)npts * sizeof(double));
+    for (int i = 0; i < npts; ++i) {
+      if (patch[i] < 0 || patch[i] >= sp->fine().npatch) bad |= 1;
+      for (int c = 0; c < 2; ++c)
+        if (!(st[2 * i + c] >= 0.0 && st[2 * i + c] <= 1.0)) bad |= 2;
+    }
   }
-  for (int i = 0; i < npts; ++i) {
-    if (ph[i] < 0 || ph[i] >= sp->fine().npatch) fail(GF_EINVAL, "patch index out of range");
-    for (int c = 0; c < 2; ++c)
-      if (!(sh[2 * i + c] >= 0.0 && sh[2 * i + c] <= 1.0)) fail(GF_EINVAL, "parameter (s, t) outside [0, 1]");
-  }
+  if (bad & 1) fail(GF_EINVAL, "patch index out of range");
+  if (bad & 2) fail(GF_EINVAL, "parameter (s, t) outside [0, 1]");
 }
 
 static void run_eval(const gf_space *csp, int npts, const int32_t *patch, const double *st, int nvec,
@@ -2847,52 +2849,31 @@ static void run_eval(const gf_space *csp, int npts, const int32_t *patch, const 
   HIPCHK(hipSetDevice(sp->ctx->device));
   hipStream_t s = sp->ctx->stream;
   const Level &F = sp->fine();
-  std::vector<int32_t> ph;
-  std::vector<double> sh;
-  check_points(sp, npts, patch, st, mem, ph, sh);
+  check_points(sp, npts, patch, st, mem);
   const std::shared_ptr<Pool> &pool = sp->ctx->pool;
-  PBuf<int> pd;
-  PBuf<double> sd;
-  if (npts > 0) {
-    pd.upload(pool, ph, s);
-    sd.upload(pool, sh, s);
+  PBuf<int> ph;
+  PBuf<double> sh;
+  if (mem == GF_HOST && npts > 0) {
+    ph.upload(pool, patch, npts, s);
+    sh.upload(pool, st, (size_t)2 * npts, s);
+    patch = ph.p;
+    st = sh.p;
   }
   const size_t nin = (size_t)nvec * (adjoint ? npts : F.N), nout = (size_t)nvec * (adjoint ? F.N : npts);
   InArray a;
   stage_in(sp->ctx, a, in, nin, mem, s);
   OutArray o;
   stage_out(sp->ctx, o, out, nout, mem);
+  PBuf<int> iw;
+  PBuf<double> w;
   if (adjoint) {
-    // per global coefficient, the (point, basis function) entries that touch it, in ascending point
-    // order: the gather then sums them in that order (no atomics, the same result on every run).  The
-    // element of a point is the one the device's basis evaluation picks (floor(u nel), clamped).
-    const int p = F.p, nb = p + 1, nel = F.nel, n1 = F.n1;
-    std::vector<int> cnt((size_t)F.N + 1, 0);
-    std::vector<int> gids((size_t)npts * nb * nb);
-    for (int i = 0; i < npts; ++i) {
-      const int ex = std::min(std::max((int)std::floor(sh[2 * i] * nel), 0), nel - 1);
-      const int ey = std::min(std::max((int)std::floor(sh[2 * i + 1] * nel), 0), nel - 1);
-      for (int aa = 0; aa < nb; ++aa)
-        for (int bb = 0; bb < nb; ++bb) {
-          const int gid = F.l2g[((size_t)ph[i] * n1 + ey + aa) * n1 + ex + bb];
-          gids[(size_t)i * nb * nb + aa * nb + bb] = gid;
-          cnt[(size_t)gid + 1] += 1;
-        }
-    }
-    for (int gi = 0; gi < F.N; ++gi) cnt[(size_t)gi + 1] += cnt[gi];
-    std::vector<int> fill(cnt.begin(), cnt.end() - 1), ent(std::max<size_t>(1, gids.size()));
-    for (size_t k = 0; k < gids.size(); ++k) ent[fill[gids[k]]++] = (int)k;
-    PBuf<int> dptr, dent;
-    PBuf<double> w;
-    dptr.upload(pool, cnt, s);
-    dent.upload(pool, ent, s);
-    w.alloc(pool, std::max<size_t>(1, gids.size()));
-    launch_eval_adjoint(F, npts, sd.p, dptr.p, dent.p, w.p, nvec, a.p, o.p, s);
-    finish_out(o, s);  // synchronises before the host lists are released
+    iw.alloc(pool, eval_adjoint_ints(F, npts));
+    w.alloc(pool, (size_t)npts * (F.p + 1) * (F.p + 1));
+    launch_eval_adjoint(F, npts, patch, st, iw.p, w.p, nvec, a.p, o.p, s);
   } else {
-    launch_eval(F, npts, pd.p, sd.p, nvec, a.p, o.p, s);
-    finish_out(o, s);
+    launch_eval(F, npts, patch, st, nvec, a.p, o.p, s);
   }
+  finish_out(o, s);
 }
 
 // The identity of the global unknowns as a patch stencil: centre coefficient 1/(number of copies)
