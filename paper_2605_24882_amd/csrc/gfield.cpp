@@ -871,19 +871,24 @@ static Plan &get_plan(gf_space *sp, const std::vector<double> &sig) {
   PBuf<double> sn;
   sn.upload(pool, sig, s);
   PBuf<double> Lf;
-  Lf.alloc(pool, (size_t)nn * sp->N0 * sp->N0);
   PBuf<int> info;
   info.alloc(pool, nn);
-  launch_coarse_factor(sp->M0.p, sp->S0.p, sp->N0, sn.p, nn, Lf.p, info.p, s);
+  // the solve applies the inverse (a dense matrix-vector product per system, all rows in parallel)
+  pl->Ainv.alloc((size_t)nn * sp->N0 * sp->N0);
+  const bool both = launch_coarse_both(sp->M0.p, sp->S0.p, sp->N0, sn.p, nn, pl->Ainv.p, info.p, s);
+  if (!both) {
+    Lf.alloc(pool, (size_t)nn * sp->N0 * sp->N0);
+    launch_coarse_factor(sp->M0.p, sp->S0.p, sp->N0, sn.p, nn, Lf.p, info.p, s);
+  }
   std::vector<int> hinfo(nn);
   HIPCHK(hipMemcpyAsync(hinfo.data(), info.p, nn * sizeof(int), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   for (int k = 0; k < nn; ++k)
     if (hinfo[k] != 0) fail(GF_EINVAL, "coarse matrix not positive definite (shift too small)");
-  // the solve applies the inverse (a dense matrix-vector product per system, all rows in parallel)
-  pl->Ainv.alloc((size_t)nn * sp->N0 * sp->N0);
-  launch_coarse_inverse(Lf.p, sp->N0, nn, pl->Ainv.p, s);
-  HIPCHK(hipStreamSynchronize(s));
+  if (!both) {
+    launch_coarse_inverse(Lf.p, sp->N0, nn, pl->Ainv.p, s);
+    HIPCHK(hipStreamSynchronize(s));
+  }
   pl->setup_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   pl->last = sp->calls;
   Plan &ref = *pl;
