@@ -2286,14 +2286,9 @@ gf_status gf_white_noise(const gf_space *csp, int32_t nsamp, const double *z, do
     stage_in(sp->ctx, zin, z, nz, mem, s);
     OutArray bout;
     stage_out(sp->ctx, bout, b, (size_t)nsamp * F.N, mem);
-    PBuf<double> ye, BL;
-    ye.alloc(sp->ctx->pool, nz);
-    const int ldb = round_up(nsamp, CT);
-    BL.alloc(sp->ctx->pool, (size_t)F.R * ldb);
-    launch_white_noise(F, zin.p, nsamp, ye.p, BL.p, ldb, s);
-    // interface sum of the per-patch contributions, then owner copies out
-    launch_interface_sum<double>(F, BL.p, ldb, ldb / CT, nullptr, s);
-    local_to_global(F, bout.p, BL.p, nsamp, 0, ldb, s);
+    PBuf<double> ye;
+    ye.alloc(sp->ctx->pool, nz / nsamp * noise_chunk(F, nsamp));
+    launch_white_noise(F, zin.p, nsamp, ye.p, bout.p, s);
     finish_out(bout, s);
   });
 }

@@ -2,6 +2,8 @@
 // operator application, stencil extraction by probing, diagonals, the element-wise
 // white-noise load and the coarse-level Cholesky factors.
 #include "gf_internal.h"
+#include "k_solve.h"
+#include "k_stencil.h"
 
 namespace gf {
 
@@ -457,11 +459,93 @@ void launch_to_f32(const double *a, float *b, int64_t n, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------ white noise (Sec. 3.3)
-// Pass 1, one thread per element: element mass matrix M_e = sum_q m_q phi_i phi_j, its lower
-// Cholesky factor, and y_e = L_e z_e for every sample.
+// Pass 1: element mass matrices M_e = sum_q m_q phi_i phi_j, their lower Cholesky factors L_e, and
+// y_e = L_e z_e for the samples s0 .. s1.  Pass 2 gathers.  Both stream: z is read once, and the pass
+// between them (y) stays small enough for the last-level cache where that leaves enough samples to pay for
+// the factorisation.  64 samples on degree 2, 64 x 64 (113 MB of z, 13 MB of loads): 280 us of kernels
+// before (one thread per element, its matrix in scratch memory on degree 3; gathered one word per cache line),
+// 130 us so; 9 samples on degree 3, 256 x 256: 10.7 -> 1.39 ms a call.
+//
+// Degrees up to 3 (at most 16 functions an element): 16 lanes per element, lane i = row i of the matrix,
+// in registers; columns of the factor and the entries of z are broadcast by DPP.
+template <int J, int NL>
+__device__ __forceinline__ void noise_mass(double (&A)[NL], double ph, double t) {
+  if constexpr (J < NL) {
+    fma_row_bcast<J, J == 0>(A[J], ph, t);
+    noise_mass<J + 1, NL>(A, ph, t);
+  }
+}
+template <int J, int K, int NL>
+__device__ __forceinline__ void noise_update(double (&A)[NL], double nl, double l) {
+  if constexpr (K < NL) {
+    fma_row_bcast<K, K == J + 1>(A[K], nl, l);
+    noise_update<J, K + 1, NL>(A, nl, l);
+  }
+}
+template <int J, int NL>
+__device__ __forceinline__ void noise_factor(double (&A)[NL], int i) {
+  if constexpr (J < NL) {
+    // (a DPP source written by the vector instruction before it needs two cycles; the compiler does not
+    // see that the asm above wrote A[J])
+    asm volatile("s_nop 1" : "+v"(A[J]));
+    const double d = sqrt(row_bcast<J>(A[J]));
+    const double l = i == J ? d : (i > J ? A[J] / d : 0.0);
+    A[J] = l;
+    noise_update<J, J + 1, NL>(A, -l, l);
+    noise_factor<J + 1, NL>(A, i);
+  }
+}
+// v = sum_{k <= i} A[k] z_k (row i reads no entry past its own: what is not finite there stays there)
+template <int K, int NL>
+__device__ __forceinline__ void noise_row(double &v, const double (&A)[NL], double z, int i) {
+  if constexpr (K < NL) {
+    double t = v;
+    fma_row_bcast<K, K == 0>(t, z, A[K]);
+    v = K <= i ? t : v;
+    noise_row<K + 1, NL>(v, A, z, i);
+  }
+}
+template <int P, int Q>
+__global__ __launch_bounds__(256) void k_noise_apply(const double *__restrict__ metric, const double *__restrict__ basis,
+                                                     const double *__restrict__ z, double *__restrict__ ye, int nel,
+                                                     int s0, int s1, int np) {
+  constexpr int NB = P + 1, NL = NB * NB, U = 4;
+  const int64_t ne_tot = (int64_t)np * nel * nel;
+  const int64_t e0 = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+  const int64_t e = e0 < ne_tot ? e0 : ne_tot - 1;  // (whole groups of lanes run, the last ones without a result)
+  const int lane = threadIdx.x & 15, i = min(lane, NL - 1);
+  const bool on = e0 < ne_tot && lane < NL;
+  const int ex = (int)(e % nel), ey = (int)((e / nel) % nel);
+  const double *Bx = basis + (size_t)ex * 2 * Q * NB, *By = basis + (size_t)ey * 2 * Q * NB, *mt = metric + e * Q * Q * 4;
+  double A[NL];
+#pragma unroll
+  for (int k = 0; k < NL; ++k) A[k] = 0.0;
+#pragma unroll 4
+  for (int q = 0; q < Q * Q; ++q) {
+    const double ph = By[(q / Q) * NB + i / NB] * Bx[(q % Q) * NB + i % NB];
+    noise_mass<0, NL>(A, ph, mt[q * 4] * ph);
+  }
+  noise_factor<0, NL>(A, i);
+  // this block's samples of s0 .. s1
+  const int ns = s1 - s0, per = (ns + gridDim.y - 1) / gridDim.y;
+  const int sa = s0 + per * blockIdx.y, sb = min(sa + per, s1);
+  for (int s = sa; s < sb; s += U) {
+    double zv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) zv[u] = z[((size_t)min(s + u, sb - 1) * ne_tot + e) * NL + i];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      double v = 0.0;
+      noise_row<0, NL>(v, A, zv[u], i);
+      if (on && s + u < sb) ye[((size_t)(s + u - s0) * ne_tot + e) * NL + i] = v;
+    }
+  }
+}
+
+// Degrees 4 and 5: one thread per element.
 template <int P, int Q>
 __global__ void k_noise_elements(const double *metric, const double *basis, const double *z, double *ye, int nel,
-                                 int nsamp, int np) {
+                                 int s0, int s1, int np) {
   constexpr int NB = P + 1, NL = NB * NB;
   const int64_t ne_tot = (int64_t)np * nel * nel;
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -494,9 +578,9 @@ __global__ void k_noise_elements(const double *metric, const double *basis, cons
       A[i][j] = v / d;
     }
   }
-  for (int s = 0; s < nsamp; ++s) {
+  for (int s = s0; s < s1; ++s) {
     const double *zs = z + ((size_t)s * ne_tot + e) * NL;
-    double *ys = ye + ((size_t)s * ne_tot + e) * NL;
+    double *ys = ye + ((size_t)(s - s0) * ne_tot + e) * NL;
     for (int i = 0; i < NL; ++i) {
       double v = 0.0;
       for (int k = 0; k <= i; ++k) v += A[i][k] * zs[k];
@@ -505,56 +589,88 @@ __global__ void k_noise_elements(const double *metric, const double *basis, cons
   }
 }
 
-// Pass 2, one thread per (coefficient row, sample): gather the element contributions of all
-// elements containing the coefficient (patch-local, before the interface sum).
-__global__ void k_noise_gather(const double *ye, double *bl, int nel, int n1, int W, int P, int nsamp, int64_t R,
-                               int ldb, int np) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= R * nsamp) return;
-  const int64_t r = id / nsamp;
-  const int s = (int)(id % nsamp);
-  const int lx = (int)(r % W) - P, ly = (int)((r / W) % W) - P, m = (int)(r / ((int64_t)W * W));
-  if (lx < 0 || lx >= n1 || ly < 0 || ly >= n1) return;
-  const int NB = P + 1, NL = NB * NB;
+// Pass 2: b[s][g] of every unknown g: the contributions of all elements that contain it, summed within each
+// patch and then over the copies.  Unknowns off the patch boundary by their number, the others by their
+// group of copies (threads N .. N + ngroups).
+template <int P>
+__global__ __launch_bounds__(256) void k_noise_gather(const double *__restrict__ ye, double *__restrict__ b, int nel,
+                                                      int n1, int W, int N, int ngroups, int np,
+                                                      const int *__restrict__ orow, const int *__restrict__ rgid,
+                                                      const int *__restrict__ gp, const int *__restrict__ gr) {
+  constexpr int NB = P + 1, NL = NB * NB;
+  const int id = blockIdx.x * 256 + threadIdx.x;
+  if (id >= N + ngroups) return;
   const int64_t ne_tot = (int64_t)np * nel * nel;
-  double v = 0.0;
-  for (int b = 0; b < NB; ++b) {
-    const int ey = ly - b;
-    if (ey < 0 || ey >= nel) continue;
-    for (int a = 0; a < NB; ++a) {
-      const int ex = lx - a;
-      if (ex < 0 || ex >= nel) continue;
-      const int64_t e = ((int64_t)m * nel + ey) * nel + ex;
-      v += ye[((size_t)s * ne_tot + e) * NL + b * NB + a];
+  const double *ys = ye + (size_t)blockIdx.y * ne_tot * NL;
+  auto patch_sum = [&](int row) {
+    const int m = row / (W * W), q = row - m * W * W, ly = q / W - P, lx = q % W - P;
+    double v = 0.0;
+#pragma unroll
+    for (int bb = 0; bb < NB; ++bb) {
+      const int ey = ly - bb;
+      if (ey < 0 || ey >= nel) continue;
+#pragma unroll
+      for (int a = 0; a < NB; ++a) {
+        const int ex = lx - a;
+        if (ex < 0 || ex >= nel) continue;
+        v += ys[(((int64_t)m * nel + ey) * nel + ex) * NL + bb * NB + a];
+      }
     }
+    return v;
+  };
+  double v = 0.0;
+  int g = id;
+  if (id < N) {
+    const int row = orow[id], q = row % (W * W), ly = q / W - P, lx = q % W - P;
+    if (lx == 0 || lx == n1 - 1 || ly == 0 || ly == n1 - 1) return;
+    v = patch_sum(row);
+  } else {
+    const int k0 = gp[id - N], k1 = gp[id - N + 1];
+    for (int k = k0; k < k1; ++k) v += patch_sum(gr[k]);
+    g = rgid[gr[k0]];
   }
-  bl[r * ldb + s] = v;
+  b[(size_t)blockIdx.y * N + g] = v;
 }
 
-void launch_white_noise(const Level &L, const double *z, int nsamp, double *ye, double *bl, int ldb, hipStream_t s) {
+// samples per pass: y within 96 MB, but at least 16 (a pass factorises every element anew)
+int noise_chunk(const Level &L, int nsamp) {
+  const int64_t per = (int64_t)L.npatch * L.nel * L.nel * (L.p + 1) * (L.p + 1) * 8;
+  return (int)std::min<int64_t>(std::min(nsamp, 16384), std::max<int64_t>(16, ((int64_t)96 << 20) / per));
+}
+
+// ye: work space for noise_chunk samples' element contributions; b: [nsamp][N]
+void launch_white_noise(const Level &L, const double *z, int nsamp, double *ye, double *b, hipStream_t s) {
   const int64_t ne_tot = (int64_t)L.npatch * L.nel * L.nel;
-  dim3 g1((unsigned)((ne_tot + 63) / 64)), b1(64);
   if (L.q != L.p + 1 && L.q != L.p + 2) fail(GF_EUNSUPPORTED, "quadrature order out of range");
   const bool q2 = L.q == L.p + 2;
-  switch (L.p) {
-#define GF_NE(PP)                                                                                            \
-  case PP:                                                                                                   \
-    if (q2)                                                                                                  \
-      hipLaunchKernelGGL((k_noise_elements<PP, PP + 2>), g1, b1, 0, s, L.metric.p, L.basis.p, z, ye, L.nel, nsamp, \
-                         L.npatch);                                                                          \
-    else                                                                                                     \
-      hipLaunchKernelGGL((k_noise_elements<PP, PP + 1>), g1, b1, 0, s, L.metric.p, L.basis.p, z, ye, L.nel, nsamp, \
-                         L.npatch);                                                                          \
+  const int chunk = noise_chunk(L, nsamp);
+  const unsigned nb = (unsigned)((ne_tot + 15) / 16);
+  for (int s0 = 0; s0 < nsamp; s0 += chunk) {
+    const int s1 = std::min(nsamp, s0 + chunk);
+    // few elements: the samples are split over blocks as well, down to four a block
+    const unsigned ny = std::max(1u, std::min((unsigned)(s1 - s0 + 3) / 4, 1024u / nb));
+    const dim3 gn(nb, ny), go((unsigned)((ne_tot + 63) / 64));
+    const dim3 gg((unsigned)((L.N + L.ngroups + 255) / 256), (unsigned)(s1 - s0));
+    switch (L.p) {
+#define GF_NE(PP, KERN, GRID, BLOCK)                                                                               \
+  case PP:                                                                                                         \
+    if (q2) hipLaunchKernelGGL((KERN<PP, PP + 2>), GRID, BLOCK, 0, s, L.metric.p, L.basis.p, z, ye, L.nel, s0, s1, \
+                               L.npatch);                                                                          \
+    else hipLaunchKernelGGL((KERN<PP, PP + 1>), GRID, BLOCK, 0, s, L.metric.p, L.basis.p, z, ye, L.nel, s0, s1,    \
+                            L.npatch);                                                                             \
+    hipLaunchKernelGGL(k_noise_gather<PP>, gg, dim3(256), 0, s, ye, b + (size_t)s0 * L.N, L.nel, L.n1, L.W, L.N,   \
+                       L.ngroups, L.npatch, L.owner_row.p, L.row_gid.p, L.grp_ptr.p, L.grp_rows.p);                \
     break;
-    GF_NE(1) GF_NE(2) GF_NE(3) GF_NE(4) GF_NE(5)
+      GF_NE(1, k_noise_apply, gn, dim3(256))
+      GF_NE(2, k_noise_apply, gn, dim3(256))
+      GF_NE(3, k_noise_apply, gn, dim3(256))
+      GF_NE(4, k_noise_elements, go, dim3(64))
+      GF_NE(5, k_noise_elements, go, dim3(64))
 #undef GF_NE
-    default: fail(GF_EUNSUPPORTED, "degree out of range");
+      default: fail(GF_EUNSUPPORTED, "degree out of range");
+    }
+    HIPCHK(hipGetLastError());
   }
-  HIPCHK(hipGetLastError());
-  const int64_t tot = L.R * nsamp;
-  hipLaunchKernelGGL(k_noise_gather, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, ye, bl, L.nel, L.n1, L.W,
-                     L.p, nsamp, L.R, ldb, L.npatch);
-  HIPCHK(hipGetLastError());
 }
 
 // ------------------------------------------------------------------ coarse Cholesky
