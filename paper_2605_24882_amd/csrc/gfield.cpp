@@ -1072,7 +1072,8 @@ static T *vcycle(gf_space *sp, Workspace &w, const SolveSpec &spec, int li, cons
   // Three-term recurrence: a step with a previous direction takes it as z - z_prev, z_prev being the
   // iterate before its input, which the output buffer still holds (the two iterate buffers swap
   // after every step); the first step after the start from zero takes it from the iterate itself
-  // (dflags bit 0)
+  // (dflags bit 0).  The start is z1 = c r / D, so that step reads no right-hand side (it is D z1 / c) and
+  // the next no previous iterate (c r / D): bit 3
   auto smooth = [&](int k, bool last, int dflags) {
     EpiArgs<T> e;
     e.kind = EPI_CHEB;
@@ -1086,6 +1087,7 @@ static T *vcycle(gf_space *sp, Workspace &w, const SolveSpec &spec, int li, cons
     e.sig = sig;
     e.cf1 = cf + (size_t)k * ldb;
     e.cf2 = cf + (size_t)(deg + k) * ldb;
+    e.cf0 = cf + (size_t)deg * ldb;
     if (last && fin_op >= 0) {
       e.dot = fin_q ? 2 : 1;
       e.q2 = fin_q;
@@ -1096,8 +1098,10 @@ static T *vcycle(gf_space *sp, Workspace &w, const SolveSpec &spec, int li, cons
     if (w.slog && li + 1 == sp->nlev()) {
       HIPCHK(hipEventCreate(&ev0));
       HIPCHK(hipEventCreate(&ev1));
-      // read z, r (and z_prev), write z_out; with the two inner products also the FP64 vector q
-      const int vecs = 3 + ((k > 0 && !(dflags & 1)) ? 1 : 0) + (e.dot == 2 ? (int)(sizeof(double) / sizeof(T)) : 0);
+      // read z, r (and z_prev; one of the two less in the steps after the first), write z_out; with the two
+      // inner products also the FP64 vector q
+      const int vecs = 3 + ((k > 0 && !(dflags & 1)) ? 1 : 0) - ((dflags & 8) && spec.kind == GF_APPLY_STENCIL ? 1 : 0) +
+                       (e.dot == 2 ? (int)(sizeof(double) / sizeof(T)) : 0);
       w.slog->entries.push_back({ev0, ev1, vecs, (int)sizeof(T), w.slog->first_phase});
     }
     apply_epi<T>(L, spec.kind, za, sig, one, e, sc, w.cs.p, act, ldb, nt, spec.rtol * spec.rtol, spec.max_iter, s,
@@ -1119,7 +1123,7 @@ static T *vcycle(gf_space *sp, Workspace &w, const SolveSpec &spec, int li, cons
     cheb_first<T, TR>(L, rsrc, rconv, za, dM, dS, sig, cf + (size_t)deg * ldb, ldb, nt, act, s, bb ? &sc : nullptr,
                       bb ? w.cs.p : nullptr);
   }
-  for (int k = 1; k < deg; ++k) smooth(k, false, k == 1 ? 1 : 0);
+  for (int k = 1; k < deg; ++k) smooth(k, false, k == 1 ? 9 : k == 2 ? 8 : 0);
   // residual, restriction, coarse correction, prolongation
   {
     EpiArgs<T> e;

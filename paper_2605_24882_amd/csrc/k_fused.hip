@@ -305,10 +305,10 @@ static void launch_apply_k(const ApplyGeom &g, int algo, const T *stM, const T *
     constexpr int PAIR = kPairRows<P, TY> ? SM_PAIR : SM_DPP;  // (the latter is not reached, see apply_fused)
     auto kern = e.rows16 ? k_stencil<T, P, TY, KIND, DOT, SM_DPP> : k_stencil<T, P, TY, KIND, DOT, PAIR>;
     if (ev0)
-      hipExtLaunchKernelGGL(kern, dim3(8 * g.q), dim3(256), 0, s, ev0, ev1, 0, g, stM, stS, x, ca, cb, e.cf1, e.cf2,
+      hipExtLaunchKernelGGL(kern, dim3(8 * g.q), dim3(256), 0, s, ev0, ev1, 0, g, stM, stS, x, ca, cb, e.cf1, e.cf2, e.cf0,
                             e.y, e.zout, e.r, partial, active, e.dflags, e.q2);
     else
-      hipLaunchKernelGGL(kern, dim3(8 * g.q), dim3(256), 0, s, g, stM, stS, x, ca, cb, e.cf1, e.cf2, e.y, e.zout,
+      hipLaunchKernelGGL(kern, dim3(8 * g.q), dim3(256), 0, s, g, stM, stS, x, ca, cb, e.cf1, e.cf2, e.cf0, e.y, e.zout,
                          e.r, partial, active, e.dflags, e.q2);
     return;
   }
@@ -483,10 +483,10 @@ static void launch_outer_p32(const ApplyGeom &g, const double *stM, const double
     if (g.TY == 4) kern = k_stencil<double, P, 4, EPI_STORE, 1, SM_DPP, float>;
   }
   if (ev0)
-    hipExtLaunchKernelGGL(kern, dim3(8 * g.q), dim3(256), 0, s, ev0, ev1, 0, g, stM, stS, p, ca, cb, e.cf1, e.cf2,
+    hipExtLaunchKernelGGL(kern, dim3(8 * g.q), dim3(256), 0, s, ev0, ev1, 0, g, stM, stS, p, ca, cb, e.cf1, e.cf2, e.cf0,
                           e.y, e.zout, e.r, partial, active, e.dflags, e.q2);
   else
-    hipLaunchKernelGGL(kern, dim3(8 * g.q), dim3(256), 0, s, g, stM, stS, p, ca, cb, e.cf1, e.cf2, e.y, e.zout, e.r,
+    hipLaunchKernelGGL(kern, dim3(8 * g.q), dim3(256), 0, s, g, stM, stS, p, ca, cb, e.cf1, e.cf2, e.cf0, e.y, e.zout, e.r,
                        partial, active, e.dflags, e.q2);
 }
 

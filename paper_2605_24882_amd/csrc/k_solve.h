@@ -119,7 +119,10 @@ struct EpiArgs {
   // CHEB: bit 0 -- the previous direction equals the input iterate (first step after a start from
   // zero: z_prev = 0, zout is not read); bit 2 -- the step has a previous direction (every step but
   // the first of a sweep; cf1 and z_prev are read only then)
+  // bit 3 -- with bit 2, in one of the two steps after a start z1 = cf0 r / D from zero: the combined-stencil
+  // kernel takes the right-hand side (bit 0) or the previous iterate from that relation instead of memory
   int dflags = 0;
+  const T *cf0 = nullptr;  // CHEB, bit 3: the scale of the first step
   // 1: (ca, cb) is the same within every aligned group of 16 columns (the combined stencil can be
   // broadcast within 16-lane rows)
   int rows16 = 0;

@@ -50,6 +50,10 @@ __device__ __forceinline__ void block_partial2(double acc0, double acc1, double 
 //    are the row's: lanes hold them once per row and broadcast them to the multiply-adds, from
 //    registers (see StencilMode).  The Jacobi diagonal of an interior row is the centre of its stencil
 //    (interior unknowns have one copy), so the smoothing step reads no diagonal vectors.
+//    The start from zero is z1 = c r / D, so the step after it needs no right-hand side (D z1 / c) and
+//    the step after that no previous iterate (c r / D): a vector less in each, of 26 passes over an FP32
+//    vector that a V-cycle with four smoothing steps makes on its level.  Bound by memory: 61 nodes of 32
+//    samples on degree 3, 256 x 256, FP32 V-cycle 745 -> 717 ms; degree 2, 64 x 64, FP64 54.3 -> 52.3 ms.
 //  * Vector memory loads return in order, so a load issued after another cannot complete first.  All
 //    loads of a step -- the window's next column, the stencils of the next step's rows and the
 //    epilogue's right-hand side and previous iterate -- are issued one step ahead, before the arithmetic
@@ -162,14 +166,15 @@ __device__ __forceinline__ double stencil_strip(const ApplyGeom &g, const T *__r
                                                 const T *__restrict__ stS, const XT *__restrict__ x,
                                                 T *__restrict__ y, T *__restrict__ zout, const T *__restrict__ r,
                                                 int m, int iy0, int x0, int x1, int64_t ct0, int lane, T *lds,
-                                                T a, T b, T a1, T a2, int dflags,
+                                                T a, T b, T a1, T a2, T a3, int dflags,
                                                 const double *__restrict__ q2, double &acc2) {
   constexpr int S = 2 * P + 1, SS = S * S, WR = TY + 2 * P, NH = (SS + 63) / 64, NCH = (SS + 15) / 16;
   constexpr int U = (P <= 3) ? S : 1;
   const int W = g.W, n1 = g.n1;
   const int64_t ldb = g.ldb;
   const int64_t pbase = (int64_t)m * W * W;
-  const bool need_zp = (KIND == EPI_CHEB) && (dflags & 4) && !(dflags & 1);
+  const bool need_zp = (KIND == EPI_CHEB) && (dflags & 4) && !(dflags & 9);
+  const bool need_r = (KIND == EPI_RESID) || ((KIND == EPI_CHEB) && (dflags & 9) != 9);
   // Buffer bases (uniform): the window's first padded row iy0 and the strip's first output row, each
   // at column tile ct0; every offset below is relative to them.  Window rows iy0 .. iy0 + TY + 2P - 1
   // are clamped into the padded patch, output rows to the last coefficient row (a clamped row is read
@@ -217,7 +222,7 @@ __device__ __forceinline__ double stencil_strip(const ApplyGeom &g, const T *__r
       nxt[k] = ldx(woff[k] + (uint32_t)(x0 + 2 * P) * colbx);
     }
   }
-  T cmn[TY][NH], csn[TY][NH], rvn[TY], zpn[TY];
+  T cmn[TY][NH], csn[TY][NH], rvn[TY] = {}, zpn[TY];
   uint32_t vst[NH];  // this lane's stencil tap, in bytes
 #pragma unroll
   for (int h = 0; h < NH; ++h) vst[h] = (uint32_t)min(h * 64 + lane, SS - 1) * E;
@@ -230,7 +235,7 @@ __device__ __forceinline__ double stencil_strip(const ApplyGeom &g, const T *__r
         cmn[t][h] = buf_ld(T(), bm, vst[h], orr * (uint32_t)(SS * E));
         csn[t][h] = buf_ld(T(), bs, vst[h], orr * (uint32_t)(SS * E));
       }
-      if (KIND != EPI_STORE) rvn[t] = buf_ld(T(), br, vo, orr * colb);
+      if (need_r) rvn[t] = buf_ld(T(), br, vo, orr * colb);
       if (need_zp) zpn[t] = buf_ld(T(), bz, vo, orr * colb);
     }
   };
@@ -331,15 +336,21 @@ __device__ __forceinline__ double stencil_strip(const ApplyGeom &g, const T *__r
         } else if (KIND == EPI_RESID) {
           buf_st(rv[t] - Az, by, vo, so);
         } else {
-          const T dp = (dflags & 4) ? ((dflags & 1) ? zc : zc - zp[t]) : T(0);
           // FP32: the hardware reciprocal (1 ulp) instead of the correctly rounded division, which
           // costs some ten vector instructions per row in this loop; D is a positive diagonal
-          T jr;
-          if constexpr (sizeof(T) == 4)
-            jr = (rv[t] - Az) * __builtin_amdgcn_rcpf(D);
-          else
-            jr = (rv[t] - Az) / D;
-          const T dn = a1 * dp + a2 * jr;
+          auto over_D = [&](T v) -> T {
+            if constexpr (sizeof(T) == 4)
+              return v * __builtin_amdgcn_rcpf(D);
+            else
+              return v / D;
+          };
+          T dn;
+          if (dflags & 8) {
+            dn = a1 * zc + over_D(a3 * rv[t] - a2 * Az);
+          } else {
+            const T dp = (dflags & 4) ? ((dflags & 1) ? zc : zc - zp[t]) : T(0);
+            dn = a1 * dp + a2 * over_D(rv[t] - Az);
+          }
           const T zo = zc + dn;
           buf_st(zo, bz, vo, so);
           if (DOT) acc += (double)rv[t] * (double)zo;
@@ -365,7 +376,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(StencilWave
 void k_stencil(ApplyGeom g, const T *__restrict__ stM, const T *__restrict__ stS,
                                                  const XT *__restrict__ x, const T *__restrict__ ca,
                                                  const T *__restrict__ cb, const T *__restrict__ cf1,
-                                                 const T *__restrict__ cf2, T *__restrict__ y, T *__restrict__ zout,
+                                                 const T *__restrict__ cf2, const T *__restrict__ cf0,
+                                                 T *__restrict__ y, T *__restrict__ zout,
                                                  const T *__restrict__ r, double *__restrict__ partial,
                                                  const int *__restrict__ active, int dflags,
                                                  const double *__restrict__ q2) {
@@ -397,13 +409,20 @@ void k_stencil(ApplyGeom g, const T *__restrict__ stM, const T *__restrict__ stS
     const int iy0 = iyb * TY;
     const int x0 = seg * g.TX, x1 = min(x0 + g.TX, g.n1);
     const T a = ca[col], b = cb[col];
-    T a1 = 0, a2 = 0;
+    T a1 = 0, a2 = 0, a3 = 0;
     if (KIND == EPI_CHEB) {
       if (dflags & 4) a1 = cf1[col];
       a2 = cf2[col];
+      if (dflags & 8) {
+        // the two steps after z1 = c0 r / D: the right-hand side is D z1 / c0, then the previous iterate
+        // c0 r / D (columns past the batch have c0 = 0)
+        const T c0 = cf0[col];
+        if (dflags & 1) a1 += c0 != T(0) ? a2 / c0 : T(0);
+        else a3 = a2 - a1 * c0;
+      }
     }
     acc = stencil_strip<T, P, TY, KIND, DOT, MODE, XT>(g, stM, stS, x, y, zout, r, m, iy0, x0, x1, (int64_t)ct * CT,
-                                                   lane, lds_all[wave], a, b, a1, a2, dflags, q2,
+                                                   lane, lds_all[wave], a, b, a1, a2, a3, dflags, q2,
                                                    acc2);
   }
   if constexpr (DOT == 2)
