@@ -305,11 +305,11 @@ static void launch_apply_k(const ApplyGeom &g, int algo, const T *stM, const T *
     constexpr int PAIR = kPairRows<P, TY> ? SM_PAIR : SM_DPP;  // (the latter is not reached, see apply_fused)
     auto kern = e.rows16 ? k_stencil<T, P, TY, KIND, DOT, SM_DPP> : k_stencil<T, P, TY, KIND, DOT, PAIR>;
     if (ev0)
-      hipExtLaunchKernelGGL(kern, dim3(8 * g.q), dim3(256), 0, s, ev0, ev1, 0, g, stM, stS, x, ca, cb, e.cf1, e.cf2, e.cf0,
-                            e.y, e.zout, e.r, partial, active, e.dflags, e.q2);
+      hipExtLaunchKernelGGL(kern, dim3(8 * (g.q + g.qi)), dim3(256), 0, s, ev0, ev1, 0, g, stM, stS, x, ca, cb, e.cf1,
+                            e.cf2, e.cf0, e.y, e.zout, e.r, e.dM, e.dS, partial, active, e.dflags, e.q2);
     else
-      hipLaunchKernelGGL(kern, dim3(8 * g.q), dim3(256), 0, s, g, stM, stS, x, ca, cb, e.cf1, e.cf2, e.cf0, e.y, e.zout,
-                         e.r, partial, active, e.dflags, e.q2);
+      hipLaunchKernelGGL(kern, dim3(8 * (g.q + g.qi)), dim3(256), 0, s, g, stM, stS, x, ca, cb, e.cf1, e.cf2, e.cf0,
+                         e.y, e.zout, e.r, e.dM, e.dS, partial, active, e.dflags, e.q2);
     return;
   }
   if constexpr (DOT == 2) {
@@ -407,6 +407,24 @@ int partial_slots(const Level &L, int ldb, int ntiles) {
   return std::max(g.nsb + ngb, kRowBlocks);
 }
 
+// Interface blocks in the strips' launch (strips of one or two rows; four rows have no registers to spare for
+// them) instead of the interface kernel after it, up to 32768 wavefronts of shared unknowns and column
+// tiles.  A launch of few tiles takes 5 to 20 us, and the kernel after it 3 to 5 us more whatever it
+// computes; the blocks beside the strips cost nothing there.  Separate / in the launch: one sample on
+// degree 2, 4 x 4, 2.14 / 1.57 ms; 7 samples on degree 3, 32 x 32, 9.17 / 7.76; six requests on 32 x 32 22.7 /
+// 19.9; 16 samples on degree 3, 64 x 64 (fit) 50.1 / 46.6; one system on degree 3, 128 x 128, 9.0 / 8.2.  Past
+// the limit the additional reads of x show: 64 samples on the torus, degree 2, 32 x 32 (43 thousand
+// wavefronts on the finest level) 43.7 with the kernel there, 45.2 with the blocks.
+constexpr int64_t kIfaceBlockWaves = 32768;
+static void iface_blocks(ApplyGeom &g, const Level &L) {
+  if (g.TY == 4 || L.ngroups == 0 || (int64_t)L.ngroups * g.ntiles > kIfaceBlockWaves) return;
+  g.ngroups = L.ngroups;
+  g.ngb = (L.ngroups + 3) / 4;
+  g.qi = xcd_q(g.ngb * g.ntiles);
+  g.gp = L.grp_ptr.p;
+  g.gr = L.grp_rows.p;
+}
+
 template <typename T>
 void apply_fused(const Level &L, const T *stM, const T *stS, const T *x, const T *ca, const T *cb,
                  const EpiArgs<T> &e, Scratch &sc, ColState *cs, int *active, int ldb, int ntiles, double tol2,
@@ -425,6 +443,7 @@ void apply_fused(const Level &L, const T *stM, const T *stS, const T *x, const T
   g.nslot2 = g.nsb + (L.ngroups + 3) / 4;
   if (e.dot == 2 && (algo != 1 || !stencil_dot2_fits(L, ldb)))
     fail(GF_EUNSUPPORTED, "two inner products in the smoothing step need the combined-stencil kernel");
+  if (algo == 1) iface_blocks(g, L);
   switch (L.p) {
     case 1: launch_apply_p<T, 1>(g, algo, stM, stS, x, ca, cb, e, sc.partial, active, s, ev0, ev1); break;
     case 2: launch_apply_p<T, 2>(g, algo, stM, stS, x, ca, cb, e, sc.partial, active, s, ev0, ev1); break;
@@ -434,7 +453,11 @@ void apply_fused(const Level &L, const T *stM, const T *stS, const T *x, const T
     default: fail(GF_EUNSUPPORTED, "degree out of range");
   }
   HIPCHK(hipGetLastError());
-  iface_finish<T>(L, x, e, sc, cs, active, ldb, ntiles, g.nsb, tol2, maxit, s);
+  if (g.ngb) {
+    if (e.dot) finalize(g.nsb + g.ngb, e.dot, e.op, sc, cs, active, ldb, ntiles, tol2, maxit, nullptr, s);
+  } else {
+    iface_finish<T>(L, x, e, sc, cs, active, ldb, ntiles, g.nsb, tol2, maxit, s);
+  }
 }
 template void apply_fused<double>(const Level &, const double *, const double *, const double *, const double *,
                                   const double *, const EpiArgs<double> &, Scratch &, ColState *, int *, int, int,
@@ -483,11 +506,11 @@ static void launch_outer_p32(const ApplyGeom &g, const double *stM, const double
     if (g.TY == 4) kern = k_stencil<double, P, 4, EPI_STORE, 1, SM_DPP, float>;
   }
   if (ev0)
-    hipExtLaunchKernelGGL(kern, dim3(8 * g.q), dim3(256), 0, s, ev0, ev1, 0, g, stM, stS, p, ca, cb, e.cf1, e.cf2, e.cf0,
-                          e.y, e.zout, e.r, partial, active, e.dflags, e.q2);
+    hipExtLaunchKernelGGL(kern, dim3(8 * (g.q + g.qi)), dim3(256), 0, s, ev0, ev1, 0, g, stM, stS, p, ca, cb, e.cf1,
+                          e.cf2, e.cf0, e.y, e.zout, e.r, e.dM, e.dS, partial, active, e.dflags, e.q2);
   else
-    hipLaunchKernelGGL(kern, dim3(8 * g.q), dim3(256), 0, s, g, stM, stS, p, ca, cb, e.cf1, e.cf2, e.cf0, e.y, e.zout, e.r,
-                       partial, active, e.dflags, e.q2);
+    hipLaunchKernelGGL(kern, dim3(8 * (g.q + g.qi)), dim3(256), 0, s, g, stM, stS, p, ca, cb, e.cf1, e.cf2, e.cf0, e.y,
+                       e.zout, e.r, e.dM, e.dS, partial, active, e.dflags, e.q2);
 }
 
 bool outer_p32_fits(const Level &L, int ldb) { return stencil_offsets_fit(L, ldb, 4, (int)sizeof(double)); }
@@ -502,6 +525,7 @@ void apply_outer_p32(const Level &L, const float *p, const double *ca, const dou
   ApplyGeom g = apply_geom(L, ldb, ntiles, tune.TY, tune.TX, tune.NC);
   g.nslot2 = g.nsb + (L.ngroups + 3) / 4;
   const double *stM = L.stM.p, *stS = L.stS.p;
+  iface_blocks(g, L);
   switch (L.p) {
     case 1: launch_outer_p32<1>(g, stM, stS, p, ca, cb, e, sc.partial, active, s, ev0, ev1); break;
     case 2: launch_outer_p32<2>(g, stM, stS, p, ca, cb, e, sc.partial, active, s, ev0, ev1); break;
@@ -511,7 +535,10 @@ void apply_outer_p32(const Level &L, const float *p, const double *ca, const dou
     default: fail(GF_EUNSUPPORTED, "degree out of range");
   }
   HIPCHK(hipGetLastError());
-  iface_finish_x<double, float>(L, p, e, sc, cs, active, ldb, ntiles, g.nsb, tol2, maxit, s);
+  if (g.ngb)
+    finalize(g.nsb + g.ngb, 1, e.op, sc, cs, active, ldb, ntiles, tol2, maxit, nullptr, s);
+  else
+    iface_finish_x<double, float>(L, p, e, sc, cs, active, ldb, ntiles, g.nsb, tol2, maxit, s);
 }
 template void iface_finish<double>(const Level &, const double *, const EpiArgs<double> &, Scratch &, ColState *,
                                    int *, int, int, int, double, int, hipStream_t);

@@ -132,6 +132,10 @@ struct ApplyGeom {
   int W, n1, ldb, ntiles, TY, NC, nseg, TX, nyb, nstrip, nsb, q;
   int grp;  // strip blocks of one column tile dispatched back to back (1: column tile fastest)
   int nslot2;  // first slot of the second set of partial sums (dot 2)
+  // interface blocks in the same launch (combined-stencil kernel): four shared unknowns each (ngb = 0: none,
+  // the interface kernel follows), the copies of unknown i at gr[gp[i]] .. gr[gp[i + 1]]
+  int ngroups = 0, ngb = 0, qi = 0;
+  const int *gp = nullptr, *gr = nullptr;
 };
 
 struct IfaceGeom {

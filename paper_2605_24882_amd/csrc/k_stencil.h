@@ -329,7 +329,8 @@ __device__ __forceinline__ double stencil_strip(const ApplyGeom &g, const T *__r
         const T zc = win[t + P][(U == S) ? (u + P) % S : P];
         const bool shared = (ix == 0) | (ix == n1 - 1) | (iy == 0) | (iy == n1 - 1);
         if (shared) {
-          buf_st(Az, by, vo, so);  // patch contribution; the interface kernel completes it
+          // patch contribution; the interface kernel completes it (interface blocks: see iface_group)
+          if (!g.ngb) buf_st(Az, by, vo, so);
         } else if (KIND == EPI_STORE) {
           buf_st(Az, by, vo, so);
           if (DOT) acc += (double)zc * (double)Az;
@@ -365,6 +366,72 @@ __device__ __forceinline__ double stencil_strip(const ApplyGeom &g, const T *__r
   return acc;
 }
 
+// One unknown shared by several patches, for one column tile, by itself: the stencil of every copy on its
+// own patch, the sum over the copies in their order, the epilogue once (the copies of an assembled
+// vector are equal) into every copy.  It reads SS values per copy where a strip's window reads a few, but
+// depends on no other block, so these blocks run beside the strips in one launch.
+template <typename T, int P, int KIND, int DOT, int MODE, typename XT>
+__device__ __forceinline__ double iface_group(const ApplyGeom &g, const T *__restrict__ stM,
+                                              const T *__restrict__ stS, const XT *__restrict__ x, T *__restrict__ y,
+                                              T *__restrict__ zout, const T *__restrict__ r,
+                                              const T *__restrict__ dM, const T *__restrict__ dS, int grp, int col,
+                                              int lane, T a, T b, T a1, T a2, int dflags,
+                                              const double *__restrict__ q2, double &acc2) {
+  constexpr int S = 2 * P + 1, SS = S * S, NCH = (SS + 15) / 16;
+  const int k0 = uni(g.gp[grp]), k1 = uni(g.gp[grp + 1]);
+  const int64_t ldb = g.ldb, own = uni(g.gr[k0]), io = own * ldb + col;
+  T rv = 0, zc = 0, zp = 0, D = 1;
+  double qv = 0.0;
+  if (KIND != EPI_STORE) rv = r[io];
+  if (KIND == EPI_CHEB) {
+    zc = (T)x[io];
+    if ((dflags & 4) && !(dflags & 1)) zp = zout[io];
+    D = a * dM[own] + b * dS[own];
+    if (DOT == 2) qv = q2[io];
+  } else if (KIND == EPI_STORE && DOT) {
+    zc = (T)x[io];
+  }
+  T s = 0;
+  for (int k = k0; k < k1; ++k) {
+    const int64_t row = uni(g.gr[k]);
+    T cc[1][NCH], c2[1][NCH], xv[S][S], ac[1] = {0}, as[1] = {0};
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      const int tap = min(16 * c + (lane & 15), SS - 1);
+      const T cm = stM[row * SS + tap], cs = stS[row * SS + tap];
+      cc[0][c] = MODE == SM_DPP ? a * cm + b * cs : cm;
+      c2[0][c] = cs;
+    }
+    const XT *x0 = x + (row - P * g.W - P) * ldb + col;
+#pragma unroll
+    for (int dx = 0; dx < S; ++dx)
+#pragma unroll
+      for (int dy = 0; dy < S; ++dy) xv[dy][dx] = (T)x0[((int64_t)dy * g.W + dx) * ldb];
+    dpp_taps<T, S, 1, 1, 0, SS>(ac, cc, xv, 0);
+    if constexpr (MODE == SM_PAIR) {
+      dpp_taps<T, S, 1, 1, 0, SS>(as, c2, xv, 0);
+      s += a * ac[0] + b * as[0];
+    } else {
+      s += ac[0];
+    }
+  }
+  double acc = 0.0;
+  T out = s;
+  if (KIND == EPI_STORE) {
+    if (DOT) acc = (double)zc * (double)s;
+  } else if (KIND == EPI_RESID) {
+    out = rv - s;
+  } else {
+    const T dp = (dflags & 4) ? ((dflags & 1) ? zc : zc - zp) : T(0);
+    out = zc + (a1 * dp + a2 * ((rv - s) / D));
+    if (DOT) acc = (double)rv * (double)out;
+    if (DOT == 2) acc2 = (double)out * qv;
+  }
+  T *dst = KIND == EPI_CHEB ? zout : y;
+  for (int k = k0; k < k1; ++k) dst[(int64_t)g.gr[k] * ldb + col] = out;
+  return acc;
+}
+
 // waves per SIMD the register allocation of a stencil kernel is held to (0: the compiler's choice)
 template <typename T, int P, int TY, int KIND, int MODE>
 struct StencilWaves {
@@ -378,19 +445,26 @@ void k_stencil(ApplyGeom g, const T *__restrict__ stM, const T *__restrict__ stS
                                                  const T *__restrict__ cb, const T *__restrict__ cf1,
                                                  const T *__restrict__ cf2, const T *__restrict__ cf0,
                                                  T *__restrict__ y, T *__restrict__ zout,
-                                                 const T *__restrict__ r, double *__restrict__ partial,
+                                                 const T *__restrict__ r, const T *__restrict__ dM,
+                                                 const T *__restrict__ dS, double *__restrict__ partial,
                                                  const int *__restrict__ active, int dflags,
                                                  const double *__restrict__ q2) {
   constexpr int SS = (2 * P + 1) * (2 * P + 1);
   __shared__ __attribute__((aligned(16))) T lds_all[4][TY * 2 * SS];
-  const int Lb = blockIdx.x;
-  const int bl = (Lb & 7) * g.q + (Lb >> 3);
-  if (bl >= g.nsb * g.ntiles) return;
+  // the strip blocks of every tile, then the interface blocks (if any), each dealt to the XCDs in
+  // contiguous runs
+  const bool iface = TY < 4 && blockIdx.x >= 8u * g.q;
+  const int Lb = iface ? blockIdx.x - 8 * g.q : blockIdx.x;
+  const int bl = (Lb & 7) * (iface ? g.qi : g.q) + (Lb >> 3);
+  if (bl >= (iface ? g.ngb : g.nsb) * g.ntiles) return;
   // groups of grp vertically adjacent strip blocks (the last group may be shorter); within a group the
   // blocks of one column tile run back to back (they share halo rows), then those of the next tile
   // (the tiles share the group's stencil rows).  grp = 1: column tile fastest
   int ct, sb;
-  {
+  if (iface) {
+    ct = bl % g.ntiles;
+    sb = g.nsb + bl / g.ntiles;
+  } else {
     const int per = g.grp * g.ntiles, gi = bl / per, rem = bl - gi * per;
     const int gs = min(g.grp, g.nsb - gi * g.grp);
     ct = rem / gs;
@@ -402,28 +476,35 @@ void k_stencil(ApplyGeom g, const T *__restrict__ stM, const T *__restrict__ stS
   const int col = ct * CT + lane;
   const int strip = sb * 4 + wave;
   double acc = 0.0, acc2 = 0.0;
-  if (strip < g.nstrip) {
-    const int iyb = strip % g.nyb;
-    const int seg = (strip / g.nyb) % g.nseg;
-    const int m = strip / (g.nyb * g.nseg);
-    const int iy0 = iyb * TY;
-    const int x0 = seg * g.TX, x1 = min(x0 + g.TX, g.n1);
+  const int grp = strip - 4 * g.nsb;  // of an interface block
+  if (iface ? grp < g.ngroups : strip < g.nstrip) {
     const T a = ca[col], b = cb[col];
     T a1 = 0, a2 = 0, a3 = 0;
     if (KIND == EPI_CHEB) {
       if (dflags & 4) a1 = cf1[col];
       a2 = cf2[col];
-      if (dflags & 8) {
+    }
+    if (iface) {
+      if constexpr (TY < 4)
+        acc = iface_group<T, P, KIND, DOT, MODE, XT>(g, stM, stS, x, y, zout, r, dM, dS, grp, col, lane, a, b, a1, a2,
+                                                     dflags, q2, acc2);
+    } else {
+      const int iyb = strip % g.nyb;
+      const int seg = (strip / g.nyb) % g.nseg;
+      const int m = strip / (g.nyb * g.nseg);
+      const int iy0 = iyb * TY;
+      const int x0 = seg * g.TX, x1 = min(x0 + g.TX, g.n1);
+      if (KIND == EPI_CHEB && (dflags & 8)) {
         // the two steps after z1 = c0 r / D: the right-hand side is D z1 / c0, then the previous iterate
         // c0 r / D (columns past the batch have c0 = 0)
         const T c0 = cf0[col];
         if (dflags & 1) a1 += c0 != T(0) ? a2 / c0 : T(0);
         else a3 = a2 - a1 * c0;
       }
+      acc = stencil_strip<T, P, TY, KIND, DOT, MODE, XT>(g, stM, stS, x, y, zout, r, m, iy0, x0, x1,
+                                                         (int64_t)ct * CT, lane, lds_all[wave], a, b, a1, a2, a3,
+                                                         dflags, q2, acc2);
     }
-    acc = stencil_strip<T, P, TY, KIND, DOT, MODE, XT>(g, stM, stS, x, y, zout, r, m, iy0, x0, x1, (int64_t)ct * CT,
-                                                   lane, lds_all[wave], a, b, a1, a2, a3, dflags, q2,
-                                                   acc2);
   }
   if constexpr (DOT == 2)
     block_partial2(acc, acc2, partial, sb, (int64_t)g.nslot2 + sb, (int)g.ldb, col);
