@@ -237,8 +237,15 @@ __global__ __launch_bounds__(kCycThreads) void k_cycle(CycleArgs<T> g) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   if (g.active && !g.active[blockIdx.x / (CT / kCycCols)]) return;
   const int j = threadIdx.x & 15, gid = threadIdx.x >> 4, col = blockIdx.x * kCycCols + j;
-  // columns that have converged (or pad the tile) take no part; all 16 of them: nothing to do
-  if (!__syncthreads_or(!g.cs[col].done)) return;
+  // columns that have converged (or pad the tile, or never had a load) need no correction; all 16 of
+  // them: it is zero, not what an earlier batch left in the buffer (their search direction takes it up,
+  // with a step of zero length)
+  if (!__syncthreads_or(!g.cs[col].done)) {
+    const CycleArg<T> &L = g.lev[g.top];
+    T *out = g.top == 0 ? L.za : L.zb;
+    for (int i = gid; i < L.nrow; i += kCycGroups) out[(int64_t)L.crow[i] * g.ldb + col] = T(0);
+    return;
+  }
   double *rhs = reinterpret_cast<double *>(smem), *sol = rhs + g.n0r * kCycCols;
   T *cb = reinterpret_cast<T *>(sol + g.n0r * kCycCols);
   T *z = cb + g.ncb * kCycCols, *z2 = z + g.nrow * kCycCols, *rr = z2 + g.nrow * kCycCols;

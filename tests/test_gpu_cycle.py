@@ -57,3 +57,22 @@ def test_one_launch_cycle_matches_separate_launches(ctx, surface, p, level, mg_l
             assert abs(st["max_iters"] - su["max_iters"]) <= 1 + 0.01 * su["max_iters"], (st, su)
             err = np.linalg.norm(x - y, axis=1) / np.linalg.norm(y, axis=1)
             assert err.max() <= 4e-11 * np.sqrt(sp.ndofs), err
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_columns_without_load_stay_zero_after_a_batch_that_was_not_finite(ctx, prec):
+    # sixteen columns without a load take no part in the coarse cycle; what an earlier batch left in its
+    # buffers (here NaN, beside one column that is solved) must not reach their solutions
+    sp = g.Space(ctx, g.Geometry(ctx, False), 2, 4)
+    b = np.random.default_rng(5).standard_normal((20, sp.ndofs))
+    bad = b.copy()
+    bad[:15] = np.nan
+    with pytest.raises(RuntimeError):
+        sp.solve_shifted(30.0, bad, precision=prec)
+    ref, _ = sp.solve_shifted(30.0, b, precision=prec)
+    with pytest.raises(RuntimeError):
+        sp.solve_shifted(30.0, bad, precision=prec)
+    b[:16] = 0.0
+    x, _ = sp.solve_shifted(30.0, b, precision=prec)
+    assert not x[:16].any()
+    assert np.abs(x[16:] - ref[16:]).max() <= 1e-9 * np.abs(ref[16:]).max()
