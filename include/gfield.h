@@ -271,7 +271,8 @@ typedef struct {
 #define GF_FLAG_TIME_APPLY 1 /* bracket each outer-CG operator launch and each finest-level smoothing
                                  launch of the dominant batch (the sinc nodes; the integer solves when
                                  beta is an integer) with HIP events; iterations are then enqueued
-                                 eagerly (no graph replay) */
+                                 eagerly (no graph replay), and the smallest spaces' V-cycle is launched
+                                 step by step (equal to its one launch up to rounding) */
 
 /* Field samples u for loads b (Sec. 3.4): n = floor(beta) integer solves A w_1 = b, A w_i = M w_{i-1},
  * then the sinc rule applied to r = M w_n (r = b if n = 0), u = sum_k omega_k x_k summed in ascending k.

@@ -980,6 +980,14 @@ static int level_degree(const gf_space *sp, const SolveSpec &spec, int li) {
   return spec.cheb;
 }
 
+// Stencil taps of the finest level (patch coefficients times taps of a row) up to which the whole V-cycle runs as
+// one launch, where a block's LDS holds it.  A smoothing step takes the block as long as its rows have
+// taps; the launch it replaces 5 us whatever its size.  Launched one by one / in one: degree 2, 4 x 4 (5400
+// taps), one sample 1.55 / 1.08 ms, 60 samples 3.4 / 2.1, 4096 systems 2.1 / 1.0; degree 1, 8 x 8 (4374), FP32,
+// 60 samples 1.93 / 1.48; degree 3, 4 x 4 (14406), FP32, 9 samples 6.3 / 4.8; degree 2, 8 x 8 (15000), FP32, one
+// sample 2.46 / 2.77, 64 samples 3.26 / 3.02; degree 4, 2 x 2 (17496), 16 systems 4.1 / 4.4.
+constexpr int64_t kCycWholeTaps = 15000;
+
 // Arguments of the V-cycle's part that runs as one launch (k_cycle.hip): levels 0 .. top, top the
 // largest below the space's finest that fits a block's LDS (top -1: none, the levels are launched one
 // by one).  Levels of that size take less time in the block than their launches do alone, at any number
@@ -988,7 +996,7 @@ static int level_degree(const gf_space *sp, const SolveSpec &spec, int li) {
 // 9.61 ms, six requests on 32 x 32 28.1 -> 24.1 ms, 64 samples in FP64 on degree 2, 64 x 64 56.6 -> 54.8 ms.
 // (With only the dense solve in the launch: 10.2, 25.6 and 55.3 ms.)
 template <typename T>
-static CycleArgs<T> cycle_args(const gf_space *sp, Workspace &w, const SolveSpec &spec) {
+static CycleArgs<T> cycle_args(const gf_space *sp, Workspace &w, const SolveSpec &spec, bool whole = false) {
   CycleArgs<T> g;
   g.top = -1;
   if (spec.kind != GF_APPLY_STENCIL || sp->lev[0]->ngroups == 0) return g;
@@ -1001,7 +1009,7 @@ static CycleArgs<T> cycle_args(const gf_space *sp, Workspace &w, const SolveSpec
   g.rgid = sp->lev[0]->row_gid.p;
   g.active = w.active.p;
   g.cs = w.cs.p;
-  for (int li = 0; li + 1 < sp->nlev() && li < kCycMaxLevels; ++li) {
+  for (int li = 0; li + (whole ? 0 : 1) < sp->nlev() && li < kCycMaxLevels; ++li) {
     const Level &L = *sp->lev[li];
     LevelWork &lw = w.lw[li];
     CycleArg<T> &c = g.lev[li];
@@ -1035,7 +1043,12 @@ static CycleArgs<T> cycle_args(const gf_space *sp, Workspace &w, const SolveSpec
       break;
     }
   }
+  if (whole && g.top + 1 < sp->nlev()) g.top = -1;
   if (g.top >= 0) cycle_layout(g);
+  if (whole && g.top >= 0) {
+    g.rfine = w.r.p;
+    if constexpr (std::is_same<T, double>::value) g.lev[g.top].r = w.r.p;
+  }
   return g;
 }
 
@@ -1208,6 +1221,8 @@ struct BatchSolve {
   // flexible beta absorbs.  It halves the bytes of the operator's window vector and of p in the
   // x/p update.  Decided in start() from the batch (shift groups, offsets).
   bool p32 = false;
+  // the whole V-cycle is one launch (decided in start(): spaces whose finest level fits a block's LDS)
+  bool whole = false;
 
   int concurrent = 1;  // batches solved together in one call (their graph branches share the GPU)
   void prepare(hipStream_t s) {
@@ -1297,6 +1312,16 @@ struct BatchSolve {
         zf = bpx<float, double>(sp, *w, spec, w->r.p, w->lw[fi].r32.p, s);
       return false;
     }
+    if (whole) {
+      if (mixed()) {
+        coarse_cycle<float>(cycle_args<float>(sp, *w, spec, true), w->ntiles, w->rows16, s);
+        zf = w->lw[fi].z32b.p;
+      } else {
+        coarse_cycle<double>(cycle_args<double>(sp, *w, spec, true), w->ntiles, w->rows16, s);
+        zd = w->lw[fi].z64b.p;
+      }
+      return false;
+    }
     if (!mixed()) {
       zd = vcycle<double, double>(sp, *w, spec, fi, w->r.p, nullptr, fin_op, &fused, s);
     } else if (fin_op == OP_BETA_FLEX && fuse_flex()) {
@@ -1314,12 +1339,15 @@ struct BatchSolve {
   // whether the mixed-precision V-cycle can take the flexible beta's two inner products in its last
   // smoothing step (stencil path on at least two levels, offsets within the kernel's 32-bit range)
   bool fuse_flex() const {
-    return spec.kind == GF_APPLY_STENCIL && sp->nlev() > 1 && stencil_dot2_fits(sp->fine(), w->ldb);
+    return spec.kind == GF_APPLY_STENCIL && sp->nlev() > 1 && !whole && stencil_dot2_fits(sp->fine(), w->ldb);
   }
 
   void start(hipStream_t s) {
     const Level &F = sp->fine();
-    p32 = mixed() && !spec.mass_shift && spec.kind == GF_APPLY_STENCIL && spec.precond == GF_PRECOND_VCYCLE &&
+    whole = spec.precond == GF_PRECOND_VCYCLE && !spec.mass_shift && sp->nlev() > 1 &&
+            !(spec.flags & GF_FLAG_TIME_APPLY) && (int64_t)F.npatch * F.n1 * F.n1 * F.S * F.S < kCycWholeTaps &&
+            (mixed() ? cycle_args<float>(sp, *w, spec, true).top : cycle_args<double>(sp, *w, spec, true).top) >= 0;
+    p32 = mixed() && !whole && !spec.mass_shift && spec.kind == GF_APPLY_STENCIL && spec.precond == GF_PRECOND_VCYCLE &&
           sp->nlev() > 1 && w->full16 && w->p32.p && outer_p32_fits(F, w->ldb);
     // the smoothing launches of the first preconditioner application are timed with the others
     w->slog = (spec.flags & GF_FLAG_TIME_APPLY) ? &slog : nullptr;
@@ -1327,7 +1355,7 @@ struct BatchSolve {
     const int ldb = w->ldb, nt = w->ntiles;
     Scratch sc = w->scratch();
     // |b|^2: taken by the V-cycle's first finest-level step where there is one, else a reduction pass
-    w->fuse_bb = spec.precond == GF_PRECOND_VCYCLE && !spec.mass_shift && sp->nlev() > 1;
+    w->fuse_bb = spec.precond == GF_PRECOND_VCYCLE && !spec.mass_shift && sp->nlev() > 1 && !whole;
     if (!w->fuse_bb)
       reduce_dot<double, double>(F, w->r.p, w->r.p, sc, ldb, nt, w->cs.p, w->active.p, OP_BB, tol2(),
                                  spec.max_iter, nullptr, s);
@@ -1381,8 +1409,8 @@ struct BatchSolve {
       update_xp<double>(F, w->x.p, w->p.p, zd, w->cs.p, w->active0.p, ldb, nt, s);
       return;
     }
-    // (a one-level space has no smoothing step to carry the update: the coarse solve is the V-cycle)
-    const bool fuse = !spec.mass_shift && spec.precond == GF_PRECOND_VCYCLE && sp->nlev() > 1;
+    // (a one-level space, or a V-cycle in one launch, has no smoothing step to carry the update)
+    const bool fuse = !spec.mass_shift && spec.precond == GF_PRECOND_VCYCLE && sp->nlev() > 1 && !whole;
     if (fuse)
       w->fuse_q = w->q.p;
     else

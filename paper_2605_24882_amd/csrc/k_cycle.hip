@@ -1,4 +1,4 @@
-// The coarse part of the multigrid V-cycle in one launch.
+// The coarse part of the multigrid V-cycle in one launch (on the smallest spaces all of it).
 //
 // The columns of a batch are independent systems, so a block that owns 16 columns can run every step
 // of the V-cycle on the coarsest levels by itself: smoothing, residual, restriction, the dense solve
@@ -282,15 +282,20 @@ __global__ __launch_bounds__(kCycThreads) void k_cycle(CycleArgs<T> g) {
   {
     const CycleArg<T> &L = g.lev[g.top];
     const int *row = c.template t<int>(L.o_row);
-    for (int i = gid; i < L.nrow; i += kCycGroups) rr[i * kCycCols + j] = L.r[c.at(row[i])];
+    for (int i = gid; i < L.nrow; i += kCycGroups) {
+      const int64_t q = c.at(row[i]);
+      rr[i * kCycCols + j] = g.rfine ? (T)g.rfine[q] : L.r[q];
+    }
     __syncthreads();
   }
   for (int l = g.top; l >= 1; --l) {
     const CycleArg<T> &L = g.lev[l];
-    c.sum_rhs(L);
+    const bool fine = g.rfine && l == g.top;
+    if (!fine) c.sum_rhs(L);
     // kept for the way back up
     const int *row = c.template t<int>(L.o_row);
-    for (int i = gid; i < L.nrow; i += kCycGroups) L.r[c.at(row[i])] = rr[i * kCycCols + j];
+    if (!fine || sizeof(T) == 4)
+      for (int i = gid; i < L.nrow; i += kCycGroups) L.r[c.at(row[i])] = rr[i * kCycCols + j];
     c.first_step(L, z);
     c.preload(L);
     __syncthreads();

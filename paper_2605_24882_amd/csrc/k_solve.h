@@ -228,7 +228,8 @@ struct CycleArg {
   const T *rcoef = nullptr, *pcoef = nullptr;
 };
 // ... and the launch: levels 0 .. top, lev[top].r holding the restricted residual (patch contributions);
-// the result is left in lev[top].zb (za when top is 0)
+// the result is left in lev[top].zb (za when top is 0).  With rfine, top is the space's finest level and its
+// right-hand side the assembled FP64 residual rfine (lev[top].r: rfine itself, or room for its FP32 copy)
 template <typename T>
 struct CycleArgs {
   int top = 0, p = 0, N0 = 0, n0r = 0, ncb = 0, nrow = 0, o_gid = 0;
@@ -238,6 +239,7 @@ struct CycleArgs {
   const double *Ainv = nullptr;
   const int *node = nullptr, *rgid = nullptr, *active = nullptr;
   const ColState *cs = nullptr;
+  const double *rfine = nullptr;
   CycleArg<T> lev[kCycMaxLevels];
 };
 template <typename T>

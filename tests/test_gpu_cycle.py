@@ -60,10 +60,19 @@ def test_one_launch_cycle_matches_separate_launches(ctx, surface, p, level, mg_l
 
 
 @pytest.mark.parametrize("prec", [0, 1])
-def test_columns_without_load_stay_zero_after_a_batch_that_was_not_finite(ctx, prec):
+@pytest.mark.parametrize("surface,p,level", [("sphere", 1, 3), ("perturbed", 2, 2), ("sphere", 3, 2), ("torus", 1, 2),
+                                             ("torus", 2, 2), ("open", 2, 2)])
+def test_whole_cycle_in_one_launch_matches_separate_launches(ctx, surface, p, level, prec):
+    # the smallest spaces, finest level included
+    test_one_launch_cycle_matches_separate_launches(ctx, surface, p, level, 0, prec)
+
+
+@pytest.mark.parametrize("level", [2, 4])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_columns_without_load_stay_zero_after_a_batch_that_was_not_finite(ctx, prec, level):
     # sixteen columns without a load take no part in the coarse cycle; what an earlier batch left in its
     # buffers (here NaN, beside one column that is solved) must not reach their solutions
-    sp = g.Space(ctx, g.Geometry(ctx, False), 2, 4)
+    sp = g.Space(ctx, g.Geometry(ctx, False), 2, level)
     b = np.random.default_rng(5).standard_normal((20, sp.ndofs))
     bad = b.copy()
     bad[:15] = np.nan
