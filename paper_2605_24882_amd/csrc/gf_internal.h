@@ -194,8 +194,8 @@ double complete_k(double q);
 // wavefront strip (1, 2 or 4) and at most TX coefficients along the strip
 struct ApplyTune {
   int TY = 1, TX = 32, NC = 1;  // NC: 64-column tiles per wavefront
-  int algo = 1;                 // 0: M and S stencils applied separately; 1: one combined stencil per
-                                // distinct shift of the column tile, loads one step ahead
+  int algo = 1;                 // 0: k_apply_fused (stencils staged through LDS, any offsets); 1: k_stencil
+                                // (stencils in registers, loads one step ahead)
   int grp = 1;                  // dispatch order of the combined-stencil kernel: groups of grp
                                 // vertically adjacent strip blocks per column tile (1: tiles fastest)
   float us = 0.f;               // measured duration of one launch

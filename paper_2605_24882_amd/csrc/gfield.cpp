@@ -559,9 +559,9 @@ struct Prec<float> {
 // kind, stencil mode) every candidate launch shape of the combined-stencil kernel is timed with HIP
 // events (one warm-up and three timed launches, all column tiles active) and the fastest is kept for the
 // lifetime of the space.  The candidates write into scratch vectors of their own, so tuning leaves the
-// caller's buffers untouched; the shape changes neither the operations nor their order for any output,
-// so the choice cannot change results.  A level whose strips exceed the kernel's 32-bit buffer offsets
-// takes the separate-stencil kernel (same launch shapes).
+// caller's buffers untouched; the shape changes how inner products are split into partial sums and which
+// blocks finish the shared unknowns, that is results by rounding only.  A level whose strips exceed the
+// kernel's 32-bit buffer offsets takes the separate-stencil kernel (same launch shapes).
 static bool g_autotune = true;
 
 template <typename T>

@@ -224,11 +224,13 @@ __global__ __launch_bounds__(256) void k_iface_finish(IfaceGeom g, const XT *__r
 // without device-scope fences in the producers.
 //
 // Bound by the latency of its loads (the producers ran on other XCDs, so they come from memory) and, with
-// many slots, by what one compute unit can read: sixteen wavefronts take slots w, w + 16, ... and keep
-// sixteen loads each in flight, only the batch's own columns are read, and the column's state is loaded
-// beside them.  Degree 2, 64 x 64 elements, one tile (491 and 1024 slots): 24 us a launch with four wavefronts of
-// four chains, 11 us so; five tiles of degree 3, 32 x 32: 10.2 -> 5.5 us.
-// The partition depends only on nslot, so the sums are bitwise reproducible.
+// many slots, by what one compute unit can read: sixteen wavefronts take every sixteenth slot and keep
+// sixteen loads each in flight, only the batch's own columns are read, a tile of few columns spreads its
+// slots over the lanes that the other columns leave, and the columns' state is loaded beside them.  Degree 2,
+// 64 x 64 elements, one tile of 16 columns (491 and twice 1024 slots): 24 us a launch with four wavefronts
+// of four chains, 11 us with sixteen, 5 us with the lanes shared out (sqrt(M) y of 16 samples 82 -> 58.6 ->
+// 50.6 ms); five tiles of degree 3, 32 x 32: 10.2 -> 5.5 us.
+// The partition depends only on nslot and the columns of the tile, so the sums are bitwise reproducible.
 constexpr int kFinWaves = 16;
 __global__ __launch_bounds__(64 * kFinWaves) void k_finalize(const double *__restrict__ partial, int nslot, int nd,
                                                              int ldb, int ncols, int op, ColState *cs, int *active, double tol2,
@@ -239,19 +241,25 @@ __global__ __launch_bounds__(64 * kFinWaves) void k_finalize(const double *__res
   if (active && !active[ct]) return;
   const int lane = threadIdx.x & 63, w = uni(threadIdx.x >> 6);
   const int col = ct * CT + lane;
+  // a tile of at most 32 columns of its own: each takes cw lanes (the next power of two), the 64 / cw groups of
+  // lanes every (64 / cw)-th slot
+  const int nc = min(CT, ncols - ct * CT);
+  int cw = CT;
+  while (cw > 1 && cw / 2 >= nc) cw /= 2;
+  const int ng = CT / cw, pc = lane & (cw - 1);
   ColState c;  // loaded while the partials are summed
   if (w == 0 && op != OP_STORE) c = cs[col];
   for (int d = 0; d < nd; ++d) {
-    const double *p = partial + (int64_t)d * nslot * ldb + col;
+    const double *p = partial + (int64_t)d * nslot * ldb + ct * CT + pc;
     double s[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) s[u] = 0.0;
-    for (int b = w; b < nslot; b += U * kFinWaves) {
+    for (int b = w * ng + lane / cw; b < nslot; b += U * kFinWaves * ng) {
       double v[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int k = b + u * kFinWaves;
-        v[u] = k < nslot && col < ncols ? p[(int64_t)k * ldb] : 0.0;
+        const int k = b + u * kFinWaves * ng;
+        v[u] = k < nslot && pc < nc ? p[(int64_t)k * ldb] : 0.0;
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) s[u] += v[u];
@@ -260,7 +268,8 @@ __global__ __launch_bounds__(64 * kFinWaves) void k_finalize(const double *__res
     for (int h = U / 2; h > 0; h /= 2)
 #pragma unroll
       for (int u = 0; u < h; ++u) s[u] += s[u + h];
-    red[d][w][lane] = s[0];
+    for (int h = cw; h < CT; h *= 2) s[0] += __shfl_xor(s[0], h);
+    red[d][w][lane] = lane < cw ? s[0] : 0.0;
   }
   __syncthreads();
   if (w != 0) return;
