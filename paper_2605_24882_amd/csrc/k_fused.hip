@@ -417,14 +417,15 @@ int partial_slots(const Level &L, int ldb, int ntiles) {
 }
 
 // Interface blocks in the strips' launch (strips of one or two rows; four rows have no registers to spare for
-// them) instead of the interface kernel after it, up to 32768 wavefronts of shared unknowns and column
+// them) instead of the interface kernel after it, up to 16384 wavefronts of shared unknowns and column
 // tiles.  A launch of few tiles takes 5 to 20 us, and the kernel after it 3 to 5 us more whatever it
 // computes; the blocks beside the strips cost nothing there.  Separate / in the launch: one sample on
 // degree 2, 4 x 4, 2.14 / 1.57 ms; 7 samples on degree 3, 32 x 32, 9.17 / 7.76; six requests on 32 x 32 22.7 /
-// 19.9; 16 samples on degree 3, 64 x 64 (fit) 50.1 / 46.6; one system on degree 3, 128 x 128, 9.0 / 8.2.  Past
-// the limit the additional reads of x show: 64 samples on the torus, degree 2, 32 x 32 (43 thousand
-// wavefronts on the finest level) 43.7 with the kernel there, 45.2 with the blocks.
-constexpr int64_t kIfaceBlockWaves = 32768;
+// 19.9; 16 samples on degree 3, 64 x 64 (fit; 8.6 thousand wavefronts on the finest level) 50.1 / 46.6; 12
+// samples on degree 2, 128 x 128 (12 thousand) 32.3 / 31.6.  With more the additional reads of x show: 20
+// thousand (20 samples on degree 3, 128 x 128) 95.2 / 95.3; 32 thousand (64 samples on degree 2, 64 x 64, FP64,
+// strips of two rows) operator and interface 233 / 249 us; 43 thousand (64 samples on the torus) 43.7 / 45.2 ms.
+constexpr int64_t kIfaceBlockWaves = 16384;
 static void iface_blocks(ApplyGeom &g, const Level &L) {
   if (g.TY == 4 || L.ngroups == 0 || (int64_t)L.ngroups * g.ntiles > kIfaceBlockWaves) return;
   g.ngroups = L.ngroups;
