@@ -144,7 +144,8 @@ def _kernel_rows(path, p, kind, value_key, last=None):
     # `path`: a CSV file or its rows
     """values of every launch of the stencil kernel with epilogue `kind` ("outer": EPI_STORE with the
     inner product, FP64; "smoother": EPI_CHEB in the V-cycle's precision, FP32 when no FP64 smoothing
-    step was launched) at the finest level (the largest grid of that kernel), in dispatch order; with
+    step was launched) at the finest level (the grid of that kernel with the largest sum of values: a
+    coarser level whose launch also holds interface blocks may have the larger grid), in dispatch order; with
     `last`, only the last that many of them (the launches of the event-timed step, which ends the run)."""
     rows = list(csv.DictReader(open(path))) if isinstance(path, str) else list(path)
     if rows and "Dispatch_Id" in rows[0]:
@@ -159,7 +160,10 @@ def _kernel_rows(path, p, kind, value_key, last=None):
             v = value_key(r)
             if v is not None:
                 out.append((grid, v))
-    big = max(g for g, _ in out)
+    total = {}
+    for g, v in out:
+        total[g] = total.get(g, 0) + v
+    big = max(total, key=total.get)
     vals = [v for g, v in out if g == big]
     return (vals[-last:] if last else vals), big
 
@@ -283,7 +287,10 @@ def trace_summary(trace_csv, p, top=25, events=None):
             if _stencil_kind(name, p, kind, vt):
                 ts.append((int(r["Start_Timestamp"]), int(r["Grid_Size_X"]),
                            (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3))
-        big = max(g for _, g, _ in ts)
+        total = collections.Counter()
+        for _, g, x in ts:
+            total[g] += x
+        big = max(total, key=total.get)  # as in _kernel_rows
         d[kind] = [x for _, g, x in sorted(ts) if g == big]
         lines += ["", f"{kind} ({'finest-level Chebyshev smoothing step' if kind == 'smoother' else 'outer CG operator'}, "
                       f"grid {big}): {len(d[kind])} launches, avg {sum(d[kind]) / len(d[kind]):.2f} us"]

@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256) void k_iface_finish(IfaceGeom g, const XT *__r
 // many slots, by what one compute unit can read: sixteen wavefronts take every sixteenth slot and keep
 // sixteen loads each in flight, only the batch's own columns are read, a tile of few columns spreads its
 // slots over the lanes that the other columns leave, and the columns' state is loaded beside them.  Degree 2,
-// 64 x 64 elements, one tile of 16 columns (491 and twice 1024 slots): 24 us a launch with four wavefronts
+// 64 x 64 elements, one column (491 and twice 1024 slots): 24 us a launch with four wavefronts
 // of four chains, 11 us with sixteen, 5 us with the lanes shared out (sqrt(M) y of 16 samples 82 -> 58.6 ->
 // 50.6 ms); five tiles of degree 3, 32 x 32: 10.2 -> 5.5 us.
 // The partition depends only on nslot and the columns of the tile, so the sums are bitwise reproducible.
