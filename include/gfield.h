@@ -23,7 +23,9 @@
  *     The library keeps no caller pointer after a call returns.
  *   - `mem` says where caller arrays live: GF_HOST (host memory; the library copies) or
  *     GF_DEVICE (device memory of the context's GPU).  All work is queued on the context's
- *     HIP stream; every call returns after that work has finished.
+ *     HIP stream; every call returns after that work has finished.  A call with device arrays starts
+ *     once the work queued on the device before it has finished, on whatever stream: inputs may come
+ *     from any stream of the caller (gf_space_apply_noalloc excepted, which waits for nothing).
  *   - Vectors of unknowns are float64 in the global numbering of the space, several
  *     vectors stored one after the other: array[v * N + i] is unknown i of vector v.
  *   - Global numbering: patches in order, then coefficient row iy, then column ix (ix fastest),

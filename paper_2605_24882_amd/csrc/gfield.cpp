@@ -2138,6 +2138,13 @@ gf_status gf_space_dofmap(const gf_space *sp, int32_t *l2g) {
   });
 }
 
+// Device arrays of the caller may still be written, or an output's memory still be in use, on other streams of the
+// device when a call begins (the caller's own stream need not be the context's): the call starts once that
+// work is done.  A wait costs some microseconds on an idle device.
+static void await_caller(int mem) {
+  if (mem == GF_DEVICE) HIPCHK(hipDeviceSynchronize());
+}
+
 // device copy of a caller array (or the caller's device pointer itself)
 struct InArray {
   const double *p = nullptr;
@@ -2182,6 +2189,7 @@ gf_status gf_space_apply(const gf_space *csp, double sigma, double s_scale, int3
     if (kind != GF_APPLY_STENCIL && kind != GF_APPLY_SUMFACT) fail(GF_EINVAL, "unknown operator kind");
     if (!std::isfinite(sigma) || !std::isfinite(s_scale)) fail(GF_EINVAL, "sigma and s_scale must be finite");
     HIPCHK(hipSetDevice(sp->ctx->device));
+    await_caller(mem);
     hipStream_t s = sp->ctx->stream;
     const Level &F = sp->fine();
     const size_t n = (size_t)nvec * F.N;
@@ -2260,6 +2268,7 @@ gf_status gf_space_transfer(const gf_space *csp, int32_t level, int32_t directio
     const int li = level - sp->lc;  // index of the finer level in the hierarchy
     if (li < 1 || li >= sp->nlev()) fail(GF_EINVAL, "level must be in lc+1 .. the space's level");
     HIPCHK(hipSetDevice(sp->ctx->device));
+    await_caller(mem);
     hipStream_t s = sp->ctx->stream;
     const Level &F = *sp->lev[li], &C = *sp->lev[li - 1];
     const Level &In = direction == GF_PROLONG ? C : F, &Out = direction == GF_PROLONG ? F : C;
@@ -2311,6 +2320,7 @@ gf_status gf_white_noise(const gf_space *csp, int32_t nsamp, const double *z, do
     if (nsamp < 1) fail(GF_EINVAL, "nsamp must be >= 1");
     if (mem != GF_HOST && mem != GF_DEVICE) fail(GF_EINVAL, "mem must be GF_HOST or GF_DEVICE");
     HIPCHK(hipSetDevice(sp->ctx->device));
+    await_caller(mem);
     hipStream_t s = sp->ctx->stream;
     const Level &F = sp->fine();
     const size_t nz = (size_t)nsamp * gf_space_noise_length(sp);
@@ -2483,6 +2493,7 @@ static void run_items(gf_context *ctx, std::vector<SampleItem> &items, const gf_
     }
     if (built) setup_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - c0).count();
   }
+  await_caller(mem);
   for (auto &it : items) {
     const size_t nv = (size_t)it.nsamp * it.sp->fine().N;
     stage_in(ctx, it.bin, it.b, nv, mem, s);
@@ -2712,6 +2723,7 @@ static void run_grad(gf_tape &t, const double *g_in, double *grad, int mem, gf_s
     if (sp->plans.size() != np)
       setup_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - c0).count();
   }
+  await_caller(mem);
   InArray gin;
   stage_in(sp->ctx, gin, g_in, (size_t)nsamp * F.N, mem, s);
   OutArray gout;
@@ -2879,6 +2891,7 @@ static void run_eval(const gf_space *csp, int npts, const int32_t *patch, const 
   if (npts < 0 || nvec < 1) fail(GF_EINVAL, "npts must be >= 0 and nvec >= 1");
   if (mem != GF_HOST && mem != GF_DEVICE) fail(GF_EINVAL, "mem must be GF_HOST or GF_DEVICE");
   HIPCHK(hipSetDevice(sp->ctx->device));
+  await_caller(mem);
   hipStream_t s = sp->ctx->stream;
   const Level &F = sp->fine();
   check_points(sp, npts, patch, st, mem);
@@ -3052,6 +3065,7 @@ gf_status gf_sqrt_mass(gf_space *sp, int32_t nsamp, const double *y, double *f, 
     const bool estimate = (lo == 0.0 && hi == 0.0);
     if (!estimate && (!(lo > 0.0) || !(hi > lo) || !std::isfinite(hi))) fail(GF_EINVAL, "need 0 < lo < hi, finite");
     HIPCHK(hipSetDevice(sp->ctx->device));
+    await_caller(mem);
     begin_call(sp);
     hipStream_t s = sp->ctx->stream;
     const Level &F = sp->fine();
@@ -3190,6 +3204,7 @@ gf_status gf_solve_shifted(gf_space *sp, int32_t nsys, const double *sigma, cons
     }
     if (distinct.size() > 4096) fail(GF_EINVAL, "at most 4096 distinct shifts per call");
     HIPCHK(hipSetDevice(sp->ctx->device));
+    await_caller(mem);
     begin_call(sp);
     hipStream_t s = sp->ctx->stream;
     const Level &F = sp->fine();
