@@ -2145,6 +2145,11 @@ static void await_caller(int mem) {
   if (mem == GF_DEVICE) HIPCHK(hipDeviceSynchronize());
 }
 
+static bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + nb && y < x + na;
+}
+
 // device copy of a caller array (or the caller's device pointer itself)
 struct InArray {
   const double *p = nullptr;
@@ -2894,17 +2899,25 @@ static void run_eval(const gf_space *csp, int npts, const int32_t *patch, const 
   await_caller(mem);
   hipStream_t s = sp->ctx->stream;
   const Level &F = sp->fine();
-  check_points(sp, npts, patch, st, mem);
+  const size_t nin = (size_t)nvec * (adjoint ? npts : F.N), nout = (size_t)nvec * (adjoint ? F.N : npts);
   const std::shared_ptr<Pool> &pool = sp->ctx->pool;
   PBuf<int> ph;
   PBuf<double> sh;
-  if (mem == GF_HOST && npts > 0) {
-    ph.upload(pool, patch, npts, s);
-    sh.upload(pool, st, (size_t)2 * npts, s);
+  auto copy_points = [&](hipMemcpyKind kind) {
+    ph.alloc(pool, npts);
+    sh.alloc(pool, (size_t)2 * npts);
+    HIPCHK(hipMemcpyAsync(ph.p, patch, npts * sizeof(int), kind, s));
+    HIPCHK(hipMemcpyAsync(sh.p, st, (size_t)2 * npts * sizeof(double), kind, s));
     patch = ph.p;
     st = sh.p;
-  }
-  const size_t nin = (size_t)nvec * (adjoint ? npts : F.N), nout = (size_t)nvec * (adjoint ? F.N : npts);
+  };
+  // the values may take the place of the points: the evaluation reads them while it writes
+  if (mem == GF_DEVICE && !adjoint && npts > 0 &&
+      (overlap(out, nout * sizeof(double), patch, npts * sizeof(int)) ||
+       overlap(out, nout * sizeof(double), st, (size_t)2 * npts * sizeof(double))))
+    copy_points(hipMemcpyDeviceToDevice);
+  check_points(sp, npts, patch, st, mem);
+  if (mem == GF_HOST && npts > 0) copy_points(hipMemcpyHostToDevice);
   InArray a;
   stage_in(sp->ctx, a, in, nin, mem, s);
   OutArray o;
