@@ -2333,9 +2333,12 @@ gf_status gf_white_noise(const gf_space *csp, int32_t nsamp, const double *z, do
     stage_in(sp->ctx, zin, z, nz, mem, s);
     OutArray bout;
     stage_out(sp->ctx, bout, b, (size_t)nsamp * F.N, mem);
+    // loads that take the place of the vectors: all of these are read before the first load is written
+    const bool over = overlap(zin.p, nz * sizeof(double), bout.p, bout.n * sizeof(double));
+    const int chunk = over ? nsamp : noise_chunk(F, nsamp);
     PBuf<double> ye;
-    ye.alloc(sp->ctx->pool, nz / nsamp * noise_chunk(F, nsamp));
-    launch_white_noise(F, zin.p, nsamp, ye.p, bout.p, s);
+    ye.alloc(sp->ctx->pool, nz / nsamp * chunk);
+    launch_white_noise(F, zin.p, nsamp, chunk, ye.p, bout.p, s);
     finish_out(bout, s);
   });
 }

@@ -635,22 +635,21 @@ __global__ __launch_bounds__(256) void k_noise_gather(const double *__restrict__
 // samples per pass: y within 96 MB, but at least 16 (a pass factorises every element anew)
 int noise_chunk(const Level &L, int nsamp) {
   const int64_t per = (int64_t)L.npatch * L.nel * L.nel * (L.p + 1) * (L.p + 1) * 8;
-  return (int)std::min<int64_t>(std::min(nsamp, 16384), std::max<int64_t>(16, ((int64_t)96 << 20) / per));
+  return (int)std::min<int64_t>(nsamp, std::max<int64_t>(16, ((int64_t)96 << 20) / per));
 }
+constexpr int kNoiseGrid = 16384;  // samples per launch of the second pass
 
-// ye: work space for noise_chunk samples' element contributions; b: [nsamp][N]
-void launch_white_noise(const Level &L, const double *z, int nsamp, double *ye, double *b, hipStream_t s) {
-  const int64_t ne_tot = (int64_t)L.npatch * L.nel * L.nel;
+// ye: work space for `chunk` samples' element contributions; b: [nsamp][N]
+void launch_white_noise(const Level &L, const double *z, int nsamp, int chunk, double *ye, double *b, hipStream_t s) {
+  const int64_t ne_tot = (int64_t)L.npatch * L.nel * L.nel, nl = ne_tot * (L.p + 1) * (L.p + 1);
   if (L.q != L.p + 1 && L.q != L.p + 2) fail(GF_EUNSUPPORTED, "quadrature order out of range");
   const bool q2 = L.q == L.p + 2;
-  const int chunk = noise_chunk(L, nsamp);
   const unsigned nb = (unsigned)((ne_tot + 15) / 16);
   for (int s0 = 0; s0 < nsamp; s0 += chunk) {
     const int s1 = std::min(nsamp, s0 + chunk);
     // few elements: the samples are split over blocks as well, down to four a block
     const unsigned ny = std::max(1u, std::min((unsigned)(s1 - s0 + 3) / 4, 1024u / nb));
     const dim3 gn(nb, ny), go((unsigned)((ne_tot + 63) / 64));
-    const dim3 gg((unsigned)((L.N + L.ngroups + 255) / 256), (unsigned)(s1 - s0));
     switch (L.p) {
 #define GF_NE(PP, KERN, GRID, BLOCK)                                                                               \
   case PP:                                                                                                         \
@@ -658,8 +657,11 @@ void launch_white_noise(const Level &L, const double *z, int nsamp, double *ye, 
                                L.npatch);                                                                          \
     else hipLaunchKernelGGL((KERN<PP, PP + 1>), GRID, BLOCK, 0, s, L.metric.p, L.basis.p, z, ye, L.nel, s0, s1,    \
                             L.npatch);                                                                             \
-    hipLaunchKernelGGL(k_noise_gather<PP>, gg, dim3(256), 0, s, ye, b + (size_t)s0 * L.N, L.nel, L.n1, L.W, L.N,   \
-                       L.ngroups, L.npatch, L.owner_row.p, L.row_gid.p, L.grp_ptr.p, L.grp_rows.p);                \
+    for (int t0 = s0; t0 < s1; t0 += kNoiseGrid) /* (the grid's second dimension) */                               \
+      hipLaunchKernelGGL(k_noise_gather<PP>,                                                                       \
+                         dim3((L.N + L.ngroups + 255) / 256, std::min(s1 - t0, kNoiseGrid)), dim3(256), 0, s,      \
+                         ye + (t0 - s0) * nl, b + (size_t)t0 * L.N, L.nel, L.n1, L.W, L.N, L.ngroups, L.npatch,    \
+                         L.owner_row.p, L.row_gid.p, L.grp_ptr.p, L.grp_rows.p);                                   \
     break;
       GF_NE(1, k_noise_apply, gn, dim3(256))
       GF_NE(2, k_noise_apply, gn, dim3(256))

@@ -256,8 +256,8 @@ void replicate_cols(const Level &L, double *Y, int ldy, const double *X, int ldx
 void quadrature_sum(const Level &L, double *u, const double *X, const double *omega, int K, int S, int ldb,
                     hipStream_t s);
 void launch_to_f32(const double *a, float *b, int64_t n, hipStream_t s);
-int noise_chunk(const Level &L, int nsamp);  // samples whose element contributions ye has to hold
-void launch_white_noise(const Level &L, const double *z, int nsamp, double *ye, double *b, hipStream_t s);
+int noise_chunk(const Level &L, int nsamp);  // samples per pass (ye holds their element contributions)
+void launch_white_noise(const Level &L, const double *z, int nsamp, int chunk, double *ye, double *b, hipStream_t s);
 // flag[0] = 1 | 2: some patch index | some parameter out of range
 void launch_check_points(const Level &L, int npts, const int *patch, const double *st, int *flag, hipStream_t s);
 // point evaluation Phi u (vals [nvec][npts]) and its transpose Phi^T r (out [nvec][N], every entry written);
