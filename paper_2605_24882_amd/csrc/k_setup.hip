@@ -632,8 +632,11 @@ __global__ __launch_bounds__(256) void k_noise_gather(const double *__restrict__
   b[(size_t)blockIdx.y * N + g] = v;
 }
 
-// samples per pass: y within 96 MB, but at least 16 (a pass factorises every element anew)
+// samples per pass: y within 96 MB, but at least 16 (a pass factorises every element anew).  Degrees 4 and 5, whose
+// factorisation by one thread takes longer than everything else, in one pass: 64 samples on degree 4, 64 x 64,
+// 16.3 ms in four passes, 6.9 in one.
 int noise_chunk(const Level &L, int nsamp) {
+  if (L.p > 3) return nsamp;
   const int64_t per = (int64_t)L.npatch * L.nel * L.nel * (L.p + 1) * (L.p + 1) * 8;
   return (int)std::min<int64_t>(nsamp, std::max<int64_t>(16, ((int64_t)96 << 20) / per));
 }
