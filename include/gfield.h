@@ -372,8 +372,9 @@ void gf_tape_destroy(gf_tape *tape);
 gf_status gf_eval(const gf_space *space, int32_t npts, const int32_t *patch, const double *st, int32_t nvec,
                   const double *u, double *vals, int32_t mem);
 /* Transpose of gf_eval: out = Phi^T r, r: [nvec][npts], out: [nvec][N].  Each coefficient sums the
- * contributions of the points that touch it in a fixed order (its copies, the elements of its support, their
- * points in ascending order; no atomics): the result is the same bit for bit on every run. */
+ * contributions of the points that touch it in an order that the points alone decide (its copies, the elements of
+ * its support, their points in ascending order, dealt to 64 partial sums where there are many; no atomics):
+ * the result is the same bit for bit on every run. */
 gf_status gf_eval_adjoint(const gf_space *space, int32_t npts, const int32_t *patch, const double *st,
                           int32_t nvec, const double *r, double *out, int32_t mem);
 

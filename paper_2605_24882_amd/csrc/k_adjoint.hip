@@ -10,6 +10,7 @@
 #include "k_solve.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace gf {
 
@@ -154,18 +155,22 @@ __global__ __launch_bounds__(256) void k_fill_bins(int npts, const int *__restri
   if (i < npts) list[bin_start(off, sums, elem[i]) + slot[i]] = i;
 }
 
-// every bin in point order, and the basis products of every point, w[i][a (P+1) + b] = B_a(t_i) B_b(s_i)
+// every bin in point order, the element columns of the points beside it, and the basis products of every point,
+// w[i][a (P+1) + b] = B_a(t_i) B_b(s_i)
 template <int P>
 __global__ __launch_bounds__(256) void k_rank_points(EvalGeom g, const double *__restrict__ st,
                                                      const int *__restrict__ elem, const int *__restrict__ off,
                                                      const int *__restrict__ sums, const int *__restrict__ list,
-                                                     int *__restrict__ sorted, double *__restrict__ w) {
+                                                     int *__restrict__ sorted, int *__restrict__ column,
+                                                     double *__restrict__ w) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= g.npts) return;
   const int e = elem[i], q0 = bin_start(off, sums, e), q1 = bin_start(off, sums, e + 1);
   int rank = 0;
+#pragma unroll 8
   for (int q = q0; q < q1; ++q) rank += list[q] < i ? 1 : 0;
   sorted[q0 + rank] = i;
+  column[q0 + rank] = e % g.nel;
   double bs[P + 1], bt[P + 1];
   span_basis<P>(st[2 * i], g.nel, bs);
   span_basis<P>(st[2 * i + 1], g.nel, bt);
@@ -177,60 +182,120 @@ __global__ __launch_bounds__(256) void k_rank_points(EvalGeom g, const double *_
 
 // out[v][gid], VC vectors at a time; unknowns off the patch boundary by their number, the others by their group of
 // copies (numbers N .. N + ngroups); coefficients no point touches get 0.  WAVE false: a thread per
-// coefficient walks its points.  WAVE true: a wavefront, its lanes sharing out each element's points, the lanes'
-// sums added in a fixed tree -- for meshes with many points per element, whose few coefficients leave the
-// chip idle otherwise (see launch_eval_adjoint).
-template <int P, bool WAVE>
+// coefficient walks its points, unless points are bunched: where the longest list of a wavefront's coefficients
+// is longer than twice the steps that all 64 lanes need for its lists one after the other, they do that instead.
+// WAVE true: a wavefront per coefficient -- for meshes with many points per element, whose few coefficients leave
+// the chip idle otherwise (see launch_eval_adjoint).  Lanes' sums are added in a fixed tree.  The walk waits for
+// its loads: all vectors of a point are loaded together (past the last vector: the last one again).
+// 20000 points in one element of 64 x 64, degree 3, 16 vectors: a call took 60.5 ms with each thread walking its lists
+// element by element and a branch around every vector's load, 1.1 so; 12000 points spread over the mesh 144 -> 87 us.
+template <int P, bool WAVE, int VC>
 __global__ __launch_bounds__(256) void k_eval_gather(EvalGeom g, const int *__restrict__ off, const int *__restrict__ sums,
-                                                     const int *__restrict__ sorted, const double *__restrict__ w,
-                                                     const double *__restrict__ r, double *__restrict__ out,
+                                                     const int *__restrict__ sorted, const int *__restrict__ column,
+                                                     const double *__restrict__ w, const double *__restrict__ r,
+                                                     double *__restrict__ out,
                                                      const int *__restrict__ orow, const int *__restrict__ rgid,
                                                      const int *__restrict__ gp, const int *__restrict__ gr) {
-  constexpr int NB = P + 1, VC = WAVE ? 4 : 8, STEP = WAVE ? 64 : 1;
+  constexpr int NB = P + 1;
   const int id = WAVE ? blockIdx.x * 4 + (threadIdx.x >> 6) : blockIdx.x * 256 + threadIdx.x;
-  const int lane = WAVE ? threadIdx.x & 63 : 0;
-  const int v0 = blockIdx.y * VC, nv = min(VC, g.nvec - v0);
-  if (id >= g.N + g.ngroups) return;
+  const int lane = threadIdx.x & 63;
+  const int v0 = blockIdx.y * VC, last = g.nvec - 1 - v0;
+  // row(patch, ly, lx) of every copy of coefficient c
+  auto copies = [&](int c, auto row) {
+    auto one = [&](int rw) {
+      const int m = rw / (g.W * g.W), q = rw - m * g.W * g.W;
+      row(m, q / g.W - P, q % g.W - P);
+    };
+    if (c < g.N) {
+      one(orow[c]);
+    } else {
+      for (int k = gp[c - g.N], k1 = gp[c - g.N + 1]; k < k1; ++k) one(gr[k]);
+    }
+  };
+  // acc[v] += every step-th point of coefficient c from the first on: the elements of a row are neighbours in the
+  // list, so that lanes with different elements of the row walk theirs at the same time
+  auto walk = [&](int c, int first, int step, double (&acc)[VC]) {
+    copies(c, [&](int m, int ly, int lx) {
+      const int x0 = max(lx - P, 0), x1 = min(lx, g.nel - 1);
+      for (int b = 0; b < NB; ++b) {
+        const int ey = ly - b;
+        if (ey < 0 || ey >= g.nel) continue;
+        const int e = (m * g.nel + ey) * g.nel, q1 = bin_start(off, sums, e + x1 + 1);
+        auto take = [&](int k, auto count) {  // that many points, loaded together
+          constexpr int K = decltype(count)::value;
+          double wi[K], rv[K][VC];
+#pragma unroll
+          for (int u = 0; u < K; ++u) {
+            const int i = sorted[k + u * step], a = lx - column[k + u * step];
+            wi[u] = w[(int64_t)i * NB * NB + b * NB + a];
+#pragma unroll
+            for (int v = 0; v < VC; ++v) rv[u][v] = r[(int64_t)(v0 + min(v, last)) * g.npts + i];
+          }
+#pragma unroll
+          for (int u = 0; u < K; ++u)
+#pragma unroll
+            for (int v = 0; v < VC; ++v) acc[v] += wi[u] * rv[u][v];
+        };
+        int k = bin_start(off, sums, e + x0) + first;
+        for (; k + 3 * step < q1; k += 4 * step) take(k, std::integral_constant<int, 4>());
+        for (; k < q1; k += step) take(k, std::integral_constant<int, 1>());
+      }
+    });
+  };
+  auto over_lanes = [&](double (&acc)[VC]) {
+#pragma unroll
+    for (int v = 0; v < VC; ++v)
+      for (int d = 32; d > 0; d /= 2) acc[v] += __shfl_xor(acc[v], d);
+  };
+  bool on = id < g.N + g.ngroups;  // (the lanes of a wavefront stay together)
+  if (on && id < g.N) {
+    const int row = orow[id], q = row % (g.W * g.W), ly = q / g.W - P, lx = q % g.W - P;
+    on = lx != 0 && lx != g.n1 - 1 && ly != 0 && ly != g.n1 - 1;
+  }
   double acc[VC];
 #pragma unroll
   for (int v = 0; v < VC; ++v) acc[v] = 0.0;
-  auto add_row = [&](int row) {
-    const int m = row / (g.W * g.W), q = row - m * g.W * g.W, ly = q / g.W - P, lx = q % g.W - P;
-    for (int b = 0; b < NB; ++b) {
-      const int ey = ly - b;
-      if (ey < 0 || ey >= g.nel) continue;
-      for (int a = 0; a < NB; ++a) {
-        const int ex = lx - a;
-        if (ex < 0 || ex >= g.nel) continue;
-        const int e = (m * g.nel + ey) * g.nel + ex, q1 = bin_start(off, sums, e + 1);
-        for (int k = bin_start(off, sums, e) + lane; k < q1; k += STEP) {
-          const int i = sorted[k];
-          const double wi = w[(int64_t)i * NB * NB + b * NB + a];
-#pragma unroll
-          for (int v = 0; v < VC; ++v)
-            if (v < nv) acc[v] += wi * r[(int64_t)(v0 + v) * g.npts + i];
-        }
-      }
-    }
-  };
-  int gid = id;
-  if (id < g.N) {
-    const int row = orow[id], q = row % (g.W * g.W), ly = q / g.W - P, lx = q % g.W - P;
-    if (lx == 0 || lx == g.n1 - 1 || ly == 0 || ly == g.n1 - 1) return;
-    add_row(row);
+  if (WAVE) {
+    if (!on) return;
+    walk(id, lane, 64, acc);
+    over_lanes(acc);
+    on = lane == 0;
   } else {
-    const int k0 = gp[id - g.N], k1 = gp[id - g.N + 1];
-    for (int k = k0; k < k1; ++k) add_row(gr[k]);
-    gid = rgid[gr[k0]];
+    int n = 0;  // points of this lane's coefficient
+    if (on)
+      copies(id, [&](int m, int ly, int lx) {
+        const int x0 = max(lx - P, 0), x1 = min(lx, g.nel - 1);
+        for (int ey = max(ly - P, 0); ey <= min(ly, g.nel - 1); ++ey) {
+          const int e = (m * g.nel + ey) * g.nel;
+          n += bin_start(off, sums, e + x1 + 1) - bin_start(off, sums, e + x0);
+        }
+      });
+    int most = n, steps = n > 0 ? n / 64 + NB : 0;  // (a list per row)
+    for (int d = 32; d > 0; d /= 2) {
+      most = max(most, __shfl_xor(most, d));
+      steps += __shfl_xor(steps, d);
+    }
+    if (most > steps) {
+      for (unsigned long long todo = __ballot(n > 0); todo; todo &= todo - 1) {
+        const int l = __builtin_ctzll(todo);
+        double t[VC];
+#pragma unroll
+        for (int v = 0; v < VC; ++v) t[v] = 0.0;
+        walk(__shfl(id, l), lane, 64, t);
+        over_lanes(t);
+        if (lane == l)
+#pragma unroll
+          for (int v = 0; v < VC; ++v) acc[v] = t[v];
+      }
+    } else if (n > 0) {
+      walk(id, 0, 1, acc);
+    }
   }
-  if (WAVE)
+  if (!on) return;
+  const int gid = id < g.N ? id : rgid[gr[gp[id - g.N]]];
 #pragma unroll
-    for (int v = 0; v < VC; ++v)
-      for (int d = 32; d > 0; d /= 2) acc[v] += __shfl_down(acc[v], d);
-  if (lane == 0)
-#pragma unroll
-    for (int v = 0; v < VC; ++v)
-      if (v < nv) out[(int64_t)(v0 + v) * g.N + gid] = acc[v];
+  for (int v = 0; v < VC; ++v)
+    if (v <= last) out[(int64_t)(v0 + v) * g.N + gid] = acc[v];
 }
 
 void launch_check_points(const Level &L, int npts, const int *patch, const double *st, int *flag, hipStream_t s) {
@@ -289,16 +354,19 @@ void launch_eval_adjoint(const Level &L, int npts, const int *patch, const doubl
   for (int v0 = 0; v0 < nvec; v0 += 4 * 16384) {  // (the grid's second dimension)
     const int nv = std::min(nvec - v0, 4 * 16384);
     const EvalGeom g = eval_geom(L, npts, nv);
-    // a wavefront per coefficient from one point an element on (evaluation and transpose, degree 3, a thread /
-    // a wavefront per coefficient: 20000 points on 32 x 32 elements 369 / 229 us, 12000 on 64 x 64 194 / 324 us)
-    const bool wave = npts >= ne;
-    const dim3 gg(wave ? (L.N + L.ngroups + 3) / 4 : (L.N + L.ngroups + 255) / 256, wave ? (nv + 3) / 4 : (nv + 7) / 8);
+    // a wavefront per coefficient from one point an element on (16 vectors, a thread / a wavefront per coefficient:
+    // 20000 points on degree 3, 32 x 32 elements, 137 / 107 us a call, 12000 on 64 x 64 87 / 171; just above the line
+    // 600 on degree 2, 8 x 8, 90 / 65, but 25000 on degree 3, 64 x 64, 105 / 192)
+    const bool wave = npts >= ne, one = nv == 1;
+    const int vc = one ? 1 : wave ? 4 : 8;
+    const dim3 gg(wave ? (L.N + L.ngroups + 3) / 4 : (L.N + L.ngroups + 255) / 256, (nv + vc - 1) / vc);
 #define GF_EA(P)                                                                                                       \
   do {                                                                                                                 \
     if (npts > 0 && v0 == 0)                                                                                           \
-      hipLaunchKernelGGL(k_rank_points<P>, gp, dim3(256), 0, s, g, st, elem, off, sums, list, sorted, w);              \
-    auto gather = wave ? k_eval_gather<P, true> : k_eval_gather<P, false>;                                             \
-    hipLaunchKernelGGL(gather, gg, dim3(256), 0, s, g, off, sums, sorted, w, r + (int64_t)v0 * npts,                   \
+      hipLaunchKernelGGL(k_rank_points<P>, gp, dim3(256), 0, s, g, st, elem, off, sums, list, sorted, slot, w);        \
+    auto gather = wave ? (one ? k_eval_gather<P, true, 1> : k_eval_gather<P, true, 4>)                                 \
+                       : (one ? k_eval_gather<P, false, 1> : k_eval_gather<P, false, 8>);                              \
+    hipLaunchKernelGGL(gather, gg, dim3(256), 0, s, g, off, sums, sorted, slot, w, r + (int64_t)v0 * npts,             \
                        out + (int64_t)v0 * L.N, L.owner_row.p, L.row_gid.p, L.grp_ptr.p, L.grp_rows.p);                \
   } while (0)
     GF_DEGREES(GF_EA)
