@@ -3029,10 +3029,10 @@ static void mass_bounds(gf_space *sp, const gf_solve_opts *o, double *lo, double
   DBuf<double> dots, Mx;
   dots.alloc(2 * CT);
   Mx.alloc((size_t)F.R * CT);
-  Scratch sc = w.scratch();
   double lam = 0.0;
   for (int it = 0; it < 8; ++it) {
     mass_solve(sp, w, std::vector<double>{0.0}, &io);
+    Scratch sc = w.scratch();  // (of the batch just solved: how the partial sums are shared out depends on its columns)
     // Rayleigh quotient x^T M x / x^T x of the new iterate, then r = x / |x|
     apply_level<double>(F, GF_APPLY_STENCIL, w.x.p, Mx.p, w.one64.p, w.zero64.p, CT, 1, nullptr, s);
     reduce_dot<double, double>(F, w.x.p, Mx.p, sc, CT, 1, nullptr, nullptr, OP_STORE, 0.0, 0, dots.p, s);
