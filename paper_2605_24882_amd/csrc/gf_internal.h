@@ -141,6 +141,10 @@ struct PBuf {
   std::shared_ptr<Pool> pool_;
 };
 
+// device data at an address that a kernel reads from memory (generic pointers would make flat loads)
+template <typename T>
+using Global = const __attribute__((address_space(1))) T *;
+
 // a typed view of device memory that something else owns
 template <typename T>
 struct DView {

@@ -379,14 +379,15 @@ struct Workspace {
   std::vector<LevelWork> lw;
   DBuf<double> one64, zero64;
   DBuf<float> one32;
-  // what a batch sets per column (shifts, nodes, CG state, active tiles, smoothing coefficients): parts of
-  // one device block that prepare() fills with one copy
+  // what a batch sets per column (shifts, nodes, CG state, active tiles, smoothing coefficients), and where the coarse
+  // inverses of its plan are: parts of one device block that prepare() fills with one copy.  Captured graphs
+  // refer to the workspace only, so that batches with other plans share them
   DBuf<char> stage;
   size_t cf_off = 0;  // where the smoothing coefficients start, levels 1, 2, ... in order
   DView<double> sig64;
   DView<float> sig32;
   DView<int> node, active;
-  DBuf<double> Ainv;  // the plan's coarse inverses, copied: captured graphs refer to the workspace only
+  DView<const double *> Ainv;
   // outer-CG fusion: while set, the finest level's first smoothing step also performs r -= alpha q
   // (q = fuse_q) and the convergence test, and records the tiles active before it in active0
   const double *fuse_q = nullptr;
@@ -491,7 +492,7 @@ static Workspace &get_workspace(gf_space *sp, int ldb, int prec, int slot = 0) {
     return o;
   };
   const size_t o_cs = part(ldb * sizeof(ColState)), o_s64 = part(ldb * sizeof(double)), o_s32 = part(ldb * sizeof(float)),
-               o_node = part(ldb * sizeof(int)), o_act = part(w->ntiles * sizeof(int));
+               o_node = part(ldb * sizeof(int)), o_act = part(w->ntiles * sizeof(int)), o_inv = part(sizeof(double *));
   w->cf_off = off;
   std::vector<size_t> o_cf(sp->nlev(), 0);
   for (int li = 1; li < sp->nlev(); ++li) o_cf[li] = part(2 * (li + 1 < sp->nlev() ? 2 : kMaxCheb) * (size_t)ldb * elem);
@@ -501,6 +502,7 @@ static Workspace &get_workspace(gf_space *sp, int ldb, int prec, int slot = 0) {
   w->sig32.p = reinterpret_cast<float *>(w->stage.p + o_s32);
   w->node.p = reinterpret_cast<int *>(w->stage.p + o_node);
   w->active.p = reinterpret_cast<int *>(w->stage.p + o_act);
+  w->Ainv.p = reinterpret_cast<const double **>(w->stage.p + o_inv);
   for (int li = 1; li < sp->nlev(); ++li) {
     if (prec == GF_PREC_FP64) w->lw[li].cf64.p = reinterpret_cast<double *>(w->stage.p + o_cf[li]);
     else w->lw[li].cf32.p = reinterpret_cast<float *>(w->stage.p + o_cf[li]);
@@ -511,8 +513,8 @@ static Workspace &get_workspace(gf_space *sp, int ldb, int prec, int slot = 0) {
   w->one64.upload(ones, sp->ctx->stream);
   w->one32.upload(onesf, sp->ctx->stream);
   w->active_h.assign(w->ntiles, 0);
-  // the batch vectors and the partial sums (the per-column scalars are negligible)
-  w->bytes = w->x.n * 8 * 4 + w->p32.n * 4 + w->partial.n * 8;
+  // the batch vectors, the partial sums and the per-column data
+  w->bytes = w->x.n * 8 * 4 + w->p32.n * 4 + w->partial.n * 8 + w->stage.n;
   for (const LevelWork &v : w->lw)
     w->bytes += (v.r64.n + v.z64a.n + v.z64b.n + v.a64.n) * 8 + (v.r32.n + v.z32a.n + v.z32b.n + v.a32.n) * 4;
   Workspace &ref = *w;
@@ -1283,13 +1285,9 @@ struct BatchSolve {
       if (mixed()) fill(reinterpret_cast<float *>(at(w->lw[li].cf32.p)));
       else fill(reinterpret_cast<double *>(at(w->lw[li].cf64.p)));
     }
+    *reinterpret_cast<const double **>(at(w->Ainv.p)) = spec.plan ? spec.plan->Ainv.p : nullptr;
     HIPCHK(hipMemcpyAsync(w->stage.p, h.data(), used, hipMemcpyHostToDevice, s));
     HIPCHK(hipStreamSynchronize(s));  // before h goes
-    if (spec.plan) {
-      const size_t na = spec.plan->Ainv.n;
-      if (w->Ainv.n < na) w->Ainv.alloc(na);
-      HIPCHK(hipMemcpyAsync(w->Ainv.p, spec.plan->Ainv.p, na * sizeof(double), hipMemcpyDeviceToDevice, s));
-    }
     HIPCHK(hipMemsetAsync(w->x.p, 0, (size_t)F.R * ldb * sizeof(double), s));
   }
 
@@ -1549,7 +1547,6 @@ static std::string graph_key(const std::vector<BatchSolve *> &items, int chunk) 
        << sp.flags << "," << w.ncols << "," << sp.precond << "," << sp.mass_shift << "," << sp.smooth_load << "," << w.rows16 << "," << it->p32 << "," << (const void *)w.x.p << "," << (const void *)w.r.p << ","
        << (const void *)w.p.p << "," << (const void *)w.p32.p << "," << (const void *)w.q.p << "," << (const void *)w.cs.p << "," << (const void *)w.partial.p << ","
        << (const void *)w.active.p << "," << (const void *)w.sig64.p;
-    os << "," << (const void *)w.Ainv.p;
     for (const LevelWork &l : w.lw)
       os << "," << (const void *)l.z64a.p << (const void *)l.z32a.p << (const void *)l.cf64.p << (const void *)l.cf32.p;
   }

@@ -31,6 +31,7 @@ template <typename T, int P, bool SAME>
 struct Cycle {
   static constexpr int S = 2 * P + 1, SS = S * S, NCH = (SS + 15) / 16;
   const CycleArgs<T> &g;
+  Global<double> Ainv;  // coarse inverses (their address is loaded first of all)
   char *tab;     // tables (offsets in CycleArg)
   T *cb, *rr;    // patch contributions of the shared rows, right-hand side of the current level
   int j, gid, col;
@@ -199,9 +200,9 @@ struct Cycle {
     for (int i = gid; i < C.nrow; i += kCycGroups) rhs[un[i] * kCycCols + j] = (double)rr[i * kCycCols + j];
     __syncthreads();
     // (SAME: the node of the block's first column, for padding columns as well)
-    const double *A = g.Ainv + (size_t)g.node[SAME ? col - j : col] * g.N0 * g.N0;
+    const Global<double> A = Ainv + (size_t)g.node[SAME ? col - j : col] * g.N0 * g.N0;
     for (int i = gid; i < g.N0; i += kCycGroups) {
-      const double *Ai = A + (size_t)i * g.N0;
+      const Global<double> Ai = A + (size_t)i * g.N0;
       double acc = 0.0;
       if (SAME) {  // the columns share the node: a chunk of the row per lane, broadcast entry by entry
         for (int c = 0; c < g.N0; c += 16) {
@@ -246,6 +247,9 @@ __global__ __launch_bounds__(kCycThreads) void k_cycle(CycleArgs<T> g) {
     for (int i = gid; i < L.nrow; i += kCycGroups) out[(int64_t)L.crow[i] * g.ldb + col] = T(0);
     return;
   }
+  const uint64_t inv = (uint64_t)(uintptr_t)*g.Ainv;  // (the same for all threads: in scalar registers)
+  const Global<double> Ainv = (Global<double>)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(inv >> 32)) << 32 |
+                                               (uint32_t)__builtin_amdgcn_readfirstlane((int)inv));
   double *rhs = reinterpret_cast<double *>(smem), *sol = rhs + g.n0r * kCycCols;
   T *cb = reinterpret_cast<T *>(sol + g.n0r * kCycCols);
   T *z = cb + g.ncb * kCycCols, *z2 = z + g.nrow * kCycCols, *rr = z2 + g.nrow * kCycCols;
@@ -273,7 +277,7 @@ __global__ __launch_bounds__(kCycThreads) void k_cycle(CycleArgs<T> g) {
     }
   }
   __syncthreads();
-  Cycle<T, P, SAME> c{g, tab, cb, rr, j, gid, col, g.sig[col]};
+  Cycle<T, P, SAME> c{g, Ainv, tab, cb, rr, j, gid, col, g.sig[col]};
   auto flip = [&] {
     T *x = z;
     z = z2;

@@ -210,7 +210,7 @@ template <typename T>
 void prolong_add(const Level &F, const Level &C, T *zf, const T *zc, int ldb, int ntiles, const int *active,
                  hipStream_t s);
 template <typename T>
-void coarse_solve(const Level &C, int N0, T *z, const T *r, const double *Ainv, const int *node, int ldb, int ntiles,
+void coarse_solve(const Level &C, int N0, T *z, const T *r, const double *const *Ainv, const int *node, int ldb, int ntiles,
                   const int *active, hipStream_t s);
 // the V-cycle's coarsest levels in one launch (k_cycle.hip): one level's data ...
 constexpr int kCycMaxLevels = 8;
@@ -236,7 +236,7 @@ struct CycleArgs {
   int64_t ldb = 0;
   size_t lds = 0;
   const T *sig = nullptr;
-  const double *Ainv = nullptr;
+  const double *const *Ainv = nullptr;
   const int *node = nullptr, *rgid = nullptr, *active = nullptr;
   const ColState *cs = nullptr;
   const double *rfine = nullptr;

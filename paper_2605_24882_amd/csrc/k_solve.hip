@@ -566,7 +566,7 @@ template void prolong_add<float>(const Level &, const Level &, float *, const fl
 // read from memory instead when they do not fit), and every copy of every unknown takes its row of
 // the inverse times that vector; the four wavefronts of the block share the rows.
 template <typename T, bool STAGED>
-__global__ __launch_bounds__(256) void k_coarse(T *z, const T *r, const double *__restrict__ Ainv,
+__global__ __launch_bounds__(256) void k_coarse(T *z, const T *r, const double *const *__restrict__ Ainv,
                                                 const int *__restrict__ node, int N0, const int *__restrict__ orow,
                                                 const int *__restrict__ rgid, int64_t R0, int ldb,
                                                 const int *__restrict__ active) {
@@ -579,7 +579,7 @@ __global__ __launch_bounds__(256) void k_coarse(T *z, const T *r, const double *
     for (int i = wave; i < N0; i += 4) sh[i * CT + lane] = (double)r[(int64_t)orow[i] * ldb + col];
     __syncthreads();
   }
-  const double *A = Ainv + (size_t)node[col] * N0 * N0;
+  const Global<double> A = (Global<double>)*Ainv + (size_t)node[col] * N0 * N0;
   // every row of the level (each copy of an unknown) takes row g of A^-1 times the right-hand side
   for (int64_t rr = wave; rr < R0; rr += 4) {
     const int g = rgid[rr];
@@ -592,7 +592,7 @@ __global__ __launch_bounds__(256) void k_coarse(T *z, const T *r, const double *
 }
 
 template <typename T>
-void coarse_solve(const Level &C, int N0, T *z, const T *r, const double *Ainv, const int *node, int ldb,
+void coarse_solve(const Level &C, int N0, T *z, const T *r, const double *const *Ainv, const int *node, int ldb,
                   int ntiles, const int *active, hipStream_t s) {
   // the right-hand sides of a column tile are staged in LDS when they fit, else read from memory
   const size_t shm = (size_t)N0 * CT * sizeof(double);
@@ -604,9 +604,9 @@ void coarse_solve(const Level &C, int N0, T *z, const T *r, const double *Ainv, 
                        C.row_gid.p, C.R, ldb, active);
   HIPCHK(hipGetLastError());
 }
-template void coarse_solve<double>(const Level &, int, double *, const double *, const double *, const int *, int,
+template void coarse_solve<double>(const Level &, int, double *, const double *, const double *const *, const int *, int,
                                    int, const int *, hipStream_t);
-template void coarse_solve<float>(const Level &, int, float *, const float *, const double *, const int *, int, int,
+template void coarse_solve<float>(const Level &, int, float *, const float *, const double *const *, const int *, int, int,
                                   const int *, hipStream_t);
 
 // ------------------------------------------------------------------ layout conversions
