@@ -160,7 +160,11 @@ enum { GF_PROLONG = 0, GF_RESTRICT = 1 };
 gf_status gf_space_transfer(const gf_space *space, int32_t level, int32_t direction, int32_t nvec, const double *x,
                             double *y, int32_t mem);
 
-/* What the space keeps cached for later calls: multigrid plans (one per list of shifts: per-level
+/* (A context besides keeps up to 1 GiB of the device memory that its calls worked in, for the next ones: the
+ * environment variable GF_POOL_CACHE_MB, read by gf_context_create, sets another bound, 0 none at all.  Any
+ * allocation of the library that finds too little memory frees those blocks, of every context, and tries again.)
+ *
+ * What the space keeps cached for later calls: multigrid plans (one per list of shifts: per-level
  * spectral bounds and the dense coarse inverses of every node, Sec. 3.5) and workspaces (batch vectors,
  * one per batch width, precision and use).  Both caches are bounded (1 GiB of coarse inverses, 96 GiB of
  * workspaces per space; the environment variables GF_PLAN_CACHE_MB and GF_WORKSPACE_CACHE_MB set

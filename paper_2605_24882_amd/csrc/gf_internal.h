@@ -28,6 +28,9 @@ void hip_check(hipError_t e, const char *what, const char *file, int line);
 #define HIPCHK(x) ::gf::hip_check((x), #x, __FILE__, __LINE__)
 
 // ------------------------------------------------------------------ device buffer
+// hipMalloc; where it finds too little memory, once more after every context's pool has freed the blocks it keeps
+void *device_alloc(size_t bytes);
+
 template <typename T>
 struct DBuf {
   T *p = nullptr;
@@ -51,7 +54,7 @@ struct DBuf {
     if (count == n && p) return;
     release();
     if (count == 0) return;
-    HIPCHK(hipMalloc((void **)&p, count * sizeof(T)));
+    p = static_cast<T *>(device_alloc(count * sizeof(T)));
     HIPCHK(hipMemset(p, 0, count * sizeof(T)));
     // the fill runs on the null stream: finish it before any other stream touches the buffer
     HIPCHK(hipDeviceSynchronize());
@@ -68,7 +71,8 @@ struct DBuf {
 
 // ------------------------------------------------------------------ call-scoped buffers
 // Device memory that a call needs while it runs and a tape while it lives.  A context keeps the blocks
-// that were given back, at most kPoolBytes of them (the oldest are freed first), because hipMalloc, its
+// that were given back, at most kPoolBytes of them (the oldest are freed first; GF_POOL_CACHE_MB, read when the
+// context is created, sets another bound), and all of them until an allocation needs their memory.  hipMalloc, its
 // fill and hipFree (each waits for the device) took most of a short call's time: operator on 50 vectors,
 // degree 3, 128 x 128 elements: 165 us of kernels in a call of 608 us.  Blocks are handed out under a lock, to
 // one holder at a time, and used on the context's stream only, so that a block's next use follows its
@@ -77,12 +81,13 @@ constexpr size_t kPoolBytes = (size_t)1 << 30;
 
 class Pool {
  public:
-  Pool() = default;
+  explicit Pool(size_t bound = kPoolBytes);
   Pool(const Pool &) = delete;
   Pool &operator=(const Pool &) = delete;
   ~Pool();
   void *take(size_t bytes, size_t *got);
   void give(void *p, size_t bytes);
+  void empty();
 
  private:
   struct Block {
@@ -90,6 +95,7 @@ class Pool {
     size_t bytes;
   };
   void trim(size_t bound);
+  const size_t bound_;
   std::mutex mu_;
   std::list<Block> free_;  // oldest first
   size_t held_ = 0;

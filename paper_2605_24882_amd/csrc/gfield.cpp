@@ -56,32 +56,26 @@ void *Pool::take(size_t bytes, size_t *got) {
       return p;
     }
   }
-  void *p = nullptr;
-  hipError_t e = hipMalloc(&p, want);
-  if (e == hipErrorOutOfMemory) {
-    (void)hipGetLastError();
-    {
-      std::lock_guard<std::mutex> lk(mu_);
-      trim(0);
-    }
-    e = hipMalloc(&p, want);
-  }
-  HIPCHK(e);
+  void *p = device_alloc(want);
   *got = want;
   return p;
 }
 void Pool::give(void *p, size_t bytes) {
   try {
-    if (bytes <= kPoolBytes / 2) {  // (a larger block would push out all the others)
+    if (bytes <= bound_ / 2) {  // (a larger block would push out all the others)
       std::lock_guard<std::mutex> lk(mu_);
       free_.push_back({p, bytes});
       held_ += bytes;
-      trim(kPoolBytes);
+      trim(bound_);
       return;
     }
   } catch (...) {  // no host memory for the list entry
   }
   (void)hipFree(p);
+}
+void Pool::empty() {
+  std::lock_guard<std::mutex> lk(mu_);
+  trim(0);
 }
 void Pool::trim(size_t bound) {
   while (held_ > bound && !free_.empty()) {
@@ -90,7 +84,45 @@ void Pool::trim(size_t bound) {
     free_.pop_front();
   }
 }
-Pool::~Pool() { trim(0); }
+
+// the pools of the process (never destroyed: a tape's pool may be the last object to go)
+struct PoolList {
+  std::mutex mu;
+  std::list<Pool *> pools;
+};
+static PoolList &pool_list() {
+  static PoolList *l = new PoolList();
+  return *l;
+}
+Pool::Pool(size_t bound) : bound_(bound) {
+  PoolList &l = pool_list();
+  std::lock_guard<std::mutex> lk(l.mu);
+  l.pools.push_back(this);
+}
+Pool::~Pool() {
+  {
+    PoolList &l = pool_list();
+    std::lock_guard<std::mutex> lk(l.mu);
+    l.pools.remove(this);
+  }
+  trim(0);
+}
+
+void *device_alloc(size_t bytes) {
+  void *p = nullptr;
+  hipError_t e = hipMalloc(&p, bytes);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    {
+      PoolList &l = pool_list();
+      std::lock_guard<std::mutex> lk(l.mu);
+      for (Pool *q : l.pools) q->empty();
+    }
+    e = hipMalloc(&p, bytes);
+  }
+  HIPCHK(e);
+  return p;
+}
 
 template <class F>
 static gf_status guarded(F &&f) {
@@ -1781,7 +1813,7 @@ static void solve_all(gf_context *ctx, std::vector<BatchSolve *> &items, bool us
     return;
   }
   if (!ctx->flag_dev) {
-    HIPCHK(hipMalloc((void **)&ctx->flag_dev, sizeof(int)));
+    ctx->flag_dev = static_cast<int *>(device_alloc(sizeof(int)));
     HIPCHK(hipHostMalloc((void **)&ctx->flag_host, sizeof(int), hipHostMallocDefault));
   }
   const std::string key = graph_key(items, kGraphChunk);
@@ -1929,7 +1961,7 @@ gf_status gf_context_create(int32_t device, void *hip_stream, gf_context **out) 
     noalloc_register(device);
     std::unique_ptr<gf_context> c(new gf_context());
     c->device = device;
-    c->pool = std::make_shared<Pool>();
+    c->pool = std::make_shared<Pool>(cache_bound("GF_POOL_CACHE_MB", kPoolBytes));
     c->stream = (hipStream_t)hip_stream;  // NULL: the device's null stream
     *out = c.release();
   });
