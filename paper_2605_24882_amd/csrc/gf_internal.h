@@ -151,6 +151,9 @@ struct PBuf {
 template <typename T>
 using Global = const __attribute__((address_space(1))) T *;
 
+// lets launches of `kernel` on the current device ask for up to `bytes` of dynamic LDS (raised once a device)
+void raise_lds(const void *kernel, size_t bytes);
+
 // a typed view of device memory that something else owns
 template <typename T>
 struct DView {

@@ -15,6 +15,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <set>
 #include <sstream>
 #include <type_traits>
 
@@ -122,6 +123,17 @@ void *device_alloc(size_t bytes) {
   }
   HIPCHK(e);
   return p;
+}
+
+void raise_lds(const void *kernel, size_t bytes) {
+  static std::mutex mu;
+  static std::set<std::pair<int, const void *>> raised;
+  int device = 0;
+  HIPCHK(hipGetDevice(&device));
+  std::lock_guard<std::mutex> lk(mu);
+  if (raised.count({device, kernel})) return;
+  HIPCHK(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+  raised.insert({device, kernel});
 }
 
 template <class F>

@@ -376,12 +376,7 @@ bool cycle_fits(size_t lds) { return lds <= kCycLds; }
 
 template <typename T, int P, bool SAME>
 static void launch_cycle(const CycleArgs<T> &g, int ntiles, hipStream_t s) {
-  static const bool ok = [] {
-    HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_cycle<T, P, SAME>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kCycLds));
-    return true;
-  }();
-  (void)ok;
+  raise_lds(reinterpret_cast<const void *>(&k_cycle<T, P, SAME>), kCycLds);
   hipLaunchKernelGGL((k_cycle<T, P, SAME>), dim3(ntiles * (CT / kCycCols)), dim3(kCycThreads), (unsigned)g.lds, s, g);
   HIPCHK(hipGetLastError());
 }

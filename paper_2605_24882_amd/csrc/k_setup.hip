@@ -756,12 +756,7 @@ bool launch_coarse_both(const double *M0, const double *S0, int N0, const double
                         hipStream_t s) {
   const size_t lds = (size_t)N0 * (N0 + 1) / 2 * sizeof(double);
   if (lds > kFactorLds) return false;
-  static const bool ok = [] {
-    HIPCHK(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_coarse_both),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFactorLds));
-    return true;
-  }();
-  (void)ok;
+  raise_lds(reinterpret_cast<const void *>(&k_coarse_both), kFactorLds);
   hipLaunchKernelGGL(k_coarse_both, dim3(nnode), dim3(256), (unsigned)lds, s, M0, S0, N0, sig, Ainv, info);
   HIPCHK(hipGetLastError());
   return true;
