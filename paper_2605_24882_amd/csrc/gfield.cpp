@@ -413,9 +413,9 @@ struct SmoothLog {
 struct Workspace {
   SmoothLog *slog = nullptr;  // set while a timed batch runs
   int ldb = 0, ntiles = 0, prec = 0;
-  // whether every aligned group of 16 columns of the current batch has one shift (see EpiArgs::rows16):
-  // with the padding columns counted as part of the group they complete (rows16), and with the padding
-  // at a shift of its own, 1 (full16)
+  // whether every aligned group of 16 columns of the current batch has one shift, the padding columns counted as
+  // part of the group they complete (rows16, see EpiArgs); and whether it has no group that padding completes
+  // either (full16): only then a mixed-precision solve stores its search direction in FP32
   int rows16 = 0, full16 = 0;
   DBuf<double> x, r, p, q;  // outer CG (FP64)
   // mixed precision: the search direction stored in FP32 (see BatchSolve::p32)
@@ -1298,12 +1298,10 @@ struct BatchSolve {
     std::fill(w->active_h.begin(), w->active_h.end(), 0);
     for (int c = 0; c < spec.ncols; ++c) w->active_h[c / CT] = 1;
     std::copy(w->active_h.begin(), w->active_h.end(), act);
-    w->rows16 = w->full16 = 1;
-    for (int c = 0; c < ldb; ++c) {
-      if (c % 16 == 0) continue;
-      if (sig[c] != sig[c - 1]) w->rows16 = w->full16 = 0;
-      if (c == spec.ncols && sig[c] != 1.0) w->full16 = 0;
-    }
+    w->rows16 = 1;
+    for (int c = 0; c < ldb; ++c)
+      if (c % 16 != 0 && sig[c] != sig[c - 1]) w->rows16 = 0;
+    w->full16 = w->rows16 && spec.ncols % 16 == 0;
     // Chebyshev coefficients of every smoothing step per system (the interval depends on the node)
     size_t used = w->cf_off;
     for (int li = 1; li < sp->nlev() && !spec.mass_shift && spec.precond == GF_PRECOND_VCYCLE; ++li) {
