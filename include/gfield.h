@@ -218,7 +218,12 @@ enum { GF_PREC_FP64 = 0, GF_PREC_MIXED = 1 };
  * level (0: the library's choice per batch -- three when columns x unknowns exceed 5e7 and the batch
  * runs alone, where memory traffic binds; nine for smaller batches, where launch latency binds and
  * fewer iterations pay, and for the first adjoint solve of gf_grad_kappa, whose load dL/du is rough;
- * seven for the requests of gf_sample_batch solved together); the coarser levels take one (two on
+ * seven for the requests of gf_sample_batch solved together; a batch alone of at least 1e7 columns x
+ * unknowns is instead solved with several degrees on the first call of its kind on the space, and the fastest is
+ * kept for later calls with as many columns of each of as many shifts whose extremes have the same powers of
+ * two, the same tolerance and the same options.  Its solution thus depends, within rtol, on what was solved on the
+ * space before, also on other values of kappa: give a degree where it has to be the same bit for bit);
+ * the coarser levels take one (two on
  * levels of more than 50,000 patch coefficients, and on every level for loads that have passed
  * through the inverse operator to an order of 1.5 or more), at most cheb_degree.  Each system
  * smooths on [b ia, b] (b: 1.1 x a power estimate of the largest eigenvalue of D^-1 A), ia between

@@ -1685,8 +1685,8 @@ static void begin_call(gf_space *sp) {
 // Smoothing degree of a batch solved alone with at least kTuneMinWork columns x unknowns (the caller
 // leaving the degree to the library): on its first solve the batch is solved once with every
 // candidate degree, eagerly from its own right-hand side, and timed with HIP events to convergence;
-// the fastest degree is kept for the space and the batch configuration (number of shifts and the powers
-// of two of their extremes, width, precision, tolerance, load), so later calls with such a batch reuse
+// the fastest degree is kept for the space and the batch configuration (number of shifts, the powers
+// of two of their extremes, the columns of each, width, precision, tolerance, load), so later calls with such a batch reuse
 // it -- also when kappa differs in every call, as in a fit of kappa: tuning for the exact shifts
 // took five of the six solves of every step there (degree 3, 64 x 64, 16 samples: 301 -> 54 ms a step).  The
 // right-hand side is restored before the solve proper.  (Predicting the iteration count from the residual reduction of the first
@@ -1713,7 +1713,8 @@ static void tune_degree(hipStream_t s, BatchSolve &b) {
       << sp0.rough_load << "," << sp0.smooth_load << "," << sp0.plan->sig.size();
   // the shifts by their extremes' powers of two
   const auto mm = std::minmax_element(sp0.plan->sig.begin(), sp0.plan->sig.end());
-  key << "," << std::ilogb(*mm.first) << "," << std::ilogb(*mm.second);
+  key << "," << std::ilogb(*mm.first) << "," << std::ilogb(*mm.second) << "|";
+  for (int c = 0; c < sp0.ncols; ++c) key << sp0.col_node[c] << ",";
   auto it = b.sp->cheb_tuned.find(key.str());
   if (it == b.sp->cheb_tuned.end()) {
     const size_t nr = (size_t)F.R * b.w->ldb;
