@@ -1030,12 +1030,13 @@ static int level_degree(const gf_space *sp, const SolveSpec &spec, int li) {
   return spec.cheb;
 }
 
-// Stencil taps of the finest level (patch coefficients times taps of a row) up to which the whole V-cycle runs as
-// one launch, where a block's LDS holds it.  A smoothing step takes the block as long as its rows have
-// taps; the launch it replaces 5 us whatever its size.  Launched one by one / in one: degree 2, 4 x 4 (5400
-// taps), one sample 1.55 / 1.08 ms, 60 samples 3.4 / 2.1, 4096 systems 2.1 / 1.0; degree 1, 8 x 8 (4374), FP32,
-// 60 samples 1.93 / 1.48; degree 3, 4 x 4 (14406), FP32, 9 samples 6.3 / 4.8; degree 2, 8 x 8 (15000), FP32, one
-// sample 2.46 / 2.77, 64 samples 3.26 / 3.02; degree 4, 2 x 2 (17496), 16 systems 4.1 / 4.4.
+// Stencil taps of the finest level (patch coefficients times taps of a row) below which the whole V-cycle runs as
+// one launch, where a block's LDS holds it (degree 3, 4 x 4: in FP32 only).  A smoothing step takes the block as
+// long as its rows have taps; the launch it replaces 5 us whatever its size.  Launched one by one / in one: degree
+// 2, 4 x 4 (5400 taps), one sample 1.55 / 1.08 ms, 60 samples 3.4 / 2.1, 4096 systems 2.1 / 1.0; degree 1, 8 x 8 (4374),
+// FP32, one sample 0.89 / 0.82, 60 samples 1.93 / 1.48; degree 3, 4 x 4 (14406), FP32, one sample 4.3 / 3.4, 9 samples
+// 6.3 / 4.8; degree 2, 8 x 8 (15000), FP32, one sample 2.46 / 2.77, 64 samples 3.26 / 3.02; degree 4, 2 x 2 (17496), 16
+// systems 4.1 / 4.4.
 constexpr int64_t kCycWholeTaps = 15000;
 
 // Arguments of the V-cycle's part that runs as one launch (k_cycle.hip): levels 0 .. top, top the
